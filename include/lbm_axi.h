@@ -161,7 +161,9 @@ int lbm_axi_init(const lbm_axi_params *params, void *dev_state, size_t dev_bytes
                  const double *phi0_host, void *hip_stream, lbm_axi_case **out);
 
 /* Enqueues nsteps >= 0 time steps (Eqs. 9-40, Sec. 2.2-2.3) on the case's
- * stream and returns without waiting.  One kernel launch per step. */
+ * stream and returns without waiting.  One kernel launch per step, or per two
+ * steps for large FP64 and FP32 cases (never while the stream is recorded into
+ * a graph); the results are the same bits. */
 int lbm_axi_step(lbm_axi_case *c, int64_t nsteps);
 
 /* Fields at the current time t (phi of Eq. 16, rho of Eq. 17, u of Eq. 32, p of
@@ -214,8 +216,8 @@ int lbm_axi_destroy(lbm_axi_case *c);
 
 /* ------------------------------------------------------------------ batches
  * Many independent cases -- any grid sizes, parameters and step counts, one
- * precision -- advanced together: every time step is one kernel launch over
- * all running cases (the same per-node arithmetic as a case run alone, so
+ * precision -- advanced together: every time step, or every two of large FP64
+ * and FP32 batches, is one kernel launch over all running cases (the same per-node arithmetic as a case run alone, so
  * their populations are bit-identical).  Runs of steps over an unchanged set
  * of running cases are captured once in a hipGraph and replayed.
  *
@@ -294,7 +296,7 @@ int lbm_axi_batch_set_config(lbm_axi_batch *b, int32_t tile_r, int32_t persisten
                              int32_t bands);
 
 /* Occupancy of the batch: slots in use, running cases, free pool bytes, and
- * the number of step launches so far.  Any pointer may be NULL. */
+ * the number of time steps launched so far.  Any pointer may be NULL. */
 int lbm_axi_batch_info(const lbm_axi_batch *b, int32_t *n_used, int32_t *n_running, size_t *free_bytes,
                        int64_t *launches);
 

@@ -68,6 +68,14 @@ __device__ __forceinline__ void pull9(const Geom &g, const T *__restrict__ src, 
     v[8] = (R)src[pull_slot<8>(g, k, j)];
 }
 
+// k x + c for k = +-2, +-4: k x is exact (also of a subnormal x), so the fused
+// form rounds once where the two operations round once, to the same value, in
+// one instruction.  The kernels are compiled without contraction: any other
+// fused product would change results, halves and quarters too (of subnormal
+// values, which lead every front of the flow).
+__device__ __forceinline__ float fma_up(float k, float x, float c) { return __builtin_fmaf(k, x, c); }
+__device__ __forceinline__ double fma_up(double k, double x, double c) { return __builtin_fma(k, x, c); }
+
 // zeroth moment with a fixed summation order (used for every phi evaluation,
 // so a node's phi is bit-identical wherever it is computed)
 template <typename R>
@@ -223,12 +231,32 @@ struct Macro {
     R phi, rho, nu, dz, dr, fsz, fsr, gzf, p, uz, ur, s_nu;
 };
 
+// What the pressure and the velocity take of a node's g: the moving
+// populations' sum and the two fluxes.
+template <typename R>
+struct GSums {
+    R moving, jz, jr;
+};
+template <typename R>
+__device__ __forceinline__ GSums<R> g_sums(const R gv[9])
+{
+    return GSums<R>{((gv[1] + gv[2]) + (gv[3] + gv[4])) + ((gv[5] + gv[6]) + (gv[7] + gv[8])),
+                    (gv[1] - gv[3]) + ((gv[5] - gv[6]) + (gv[8] - gv[7])),
+                    (gv[2] - gv[4]) + ((gv[5] + gv[6]) - (gv[7] + gv[8]))};
+}
+
 // Eqs. 16-17, 35, 2-4 (with mu~ of Sec. 2.1), 33, 32, with the pressure taken
 // from the previous step's velocity (Eq. 33 needs u, Eq. 32 needs p).
-template <typename R>
+// MODE: the collision form where it is known at compile time, else FORM_OF_P.
+constexpr int FORM_OF_P = -1;
+template <int MODE, typename R>
 __device__ __forceinline__ void macro_state(const Phys<R> &P, R r, R ir, const Stencil<R> &st,
-                                            const R gv[9], R uzp, R urp, Macro<R> &m)
+                                            const GSums<R> &gs, R uzp, R urp, Macro<R> &m)
 {
+    constexpr bool UNIT = MODE == 1;                // COLLIDE_MRT_UNIT: s_2^g = 1, no free s_1
+    const bool srt = MODE == FORM_OF_P ? P.srt != 0 : MODE == 2;
+    const bool nmrt = MODE == FORM_OF_P ? P.nmrt != 0 : MODE == 3;
+    const bool free_s1 = !UNIT && P.free_s1;
     R phi = st.c;
     m.phi = phi;
     m.rho = P.rho_g + phi * P.drho;
@@ -243,26 +271,30 @@ __device__ __forceinline__ void macro_state(const Phys<R> &P, R r, R ir, const S
 
     R tau_g = (R)3 * m.nu + (R)0.5;                 // Eq. 34, c_s^2 = 1/3
     m.s_nu = div_r((R)1, tau_g);
-    R s2 = P.srt ? m.s_nu : P.sg2;
+    R s2 = srt ? m.s_nu : (UNIT ? (R)1 : P.sg2);
     // the energy moment's rate: 1/tau_g (Eq. 34), or its own with free_s1
-    R s1 = P.free_s1 ? P.sg[1] : m.s_nu;
-    R itau1 = P.free_s1 ? P.isg1 : tau_g;
+    R s1 = free_s1 ? P.sg[1] : m.s_nu;
+    R itau1 = free_s1 ? P.isg1 : tau_g;
     // Eq. 33's coefficient; for the raw-moment basis the same Chapman-Enskog
     // step (Appendix C) gives (3/s_c - 1/s_q - 1)/2, s_c = s_1 the rate of
     // c_z^2 + c_r^2 and s_q = s_2^g that of c_z^2 c_r^2
-    R s_p = P.nmrt ? (R)0.5 * ((R)3 * itau1 - P.isg2 - (R)1)
+    R s_p = nmrt ? (R)0.5 * ((R)3 * itau1 - P.isg2 - (R)1)
                    : div_r(s1 + s2 - s1 * s2, (R)2 * s1 * s2);
 
-    R g_moving = ((gv[1] + gv[2]) + (gv[3] + gv[4])) + ((gv[5] + gv[6]) + (gv[7] + gv[8]));
     R ugr = P.drho * (uzp * m.dz + urp * m.dr);
     // c_s^2/(1-w0) = 3/5;  rho s_0(u) = -(2/3) rho |u|^2;  w0 = 4/9
-    m.p = (R)0.6 * (g_moving * ir + (R)0.5 * ugr - (R)(2.0 / 3.0) * m.rho * (uzp * uzp + urp * urp) -
+    m.p = (R)0.6 * (gs.moving * ir + (R)0.5 * ugr - (R)(2.0 / 3.0) * m.rho * (uzp * uzp + urp * urp) -
                     s_p * (R)(4.0 / 9.0) * m.rho * urp * ir);
 
-    R jz = (gv[1] - gv[3]) + ((gv[5] - gv[6]) + (gv[8] - gv[7]));
-    R jr = (gv[2] - gv[4]) + ((gv[5] + gv[6]) - (gv[7] + gv[8]));
-    m.uz = (jz + (R)0.5 * r * (m.fsz + m.gzf)) / (r * m.rho);
-    m.ur = (jr + (R)0.5 * (r * m.fsr + m.p)) / (r * m.rho + m.rho * m.nu * ir);
+    m.uz = (gs.jz + (R)0.5 * r * (m.fsz + m.gzf)) / (r * m.rho);
+    m.ur = (gs.jr + (R)0.5 * (r * m.fsr + m.p)) / (r * m.rho + m.rho * m.nu * ir);
+}
+
+template <int MODE, typename R>
+__device__ __forceinline__ void macro_state(const Phys<R> &P, R r, R ir, const Stencil<R> &st,
+                                            const R gv[9], R uzp, R urp, Macro<R> &m)
+{
+    macro_state<MODE>(P, r, ir, st, g_sums(gv), uzp, urp, m);
 }
 
 // m = M v for the matrix of Sec. 2.2
@@ -274,12 +306,12 @@ __device__ __forceinline__ void to_moments(const R v[9], R m[9])
     R qz = (v[5] - v[6]) - (v[7] - v[8]);
     R qr = (v[5] + v[6]) - (v[7] + v[8]);
     m[0] = v[0] + axis + diag;
-    m[1] = (R)-4 * v[0] - axis + (R)2 * diag;
-    m[2] = (R)4 * v[0] - (R)2 * axis + diag;
+    m[1] = fma_up((R)2, diag, fma_up((R)-4, v[0], -axis));
+    m[2] = fma_up((R)-2, axis, (R)4 * v[0]) + diag;
     m[3] = (v[1] - v[3]) + qz;
-    m[4] = (R)-2 * (v[1] - v[3]) + qz;
+    m[4] = fma_up((R)-2, v[1] - v[3], qz);
     m[5] = (v[2] - v[4]) + qr;
-    m[6] = (R)-2 * (v[2] - v[4]) + qr;
+    m[6] = fma_up((R)-2, v[2] - v[4], qr);
     m[7] = (v[1] - v[2]) + (v[3] - v[4]);
     m[8] = (v[5] - v[6]) + (v[7] - v[8]);
 }
@@ -292,11 +324,11 @@ __device__ __forceinline__ void from_moments(const R m[9], R v[9])
     R n0 = m[0] * (R)(1.0 / 9.0), n1 = m[1] * (R)(1.0 / 36.0), n2 = m[2] * (R)(1.0 / 36.0);
     R n3 = m[3] * (R)(1.0 / 6.0), n4 = m[4] * (R)(1.0 / 12.0), n5 = m[5] * (R)(1.0 / 6.0);
     R n6 = m[6] * (R)(1.0 / 12.0), n7 = m[7] * (R)0.25, n8 = m[8] * (R)0.25;
-    R base_a = n0 - n1 - (R)2 * n2;            // links 1-4
-    R base_d = n0 + (R)2 * n1 + n2;            // links 5-8
-    R xz = n3 - (R)2 * n4, xr = n5 - (R)2 * n6;
+    R base_a = fma_up((R)-2, n2, n0 - n1);     // links 1-4
+    R base_d = fma_up((R)2, n1, n0) + n2;      // links 5-8
+    R xz = fma_up((R)-2, n4, n3), xr = fma_up((R)-2, n6, n5);
     R yz = n3 + n4, yr = n5 + n6;
-    v[0] = n0 - (R)4 * n1 + (R)4 * n2;
+    v[0] = fma_up((R)4, n2, fma_up((R)-4, n1, n0));
     v[1] = base_a + xz + n7;
     v[2] = base_a + xr - n7;
     v[3] = base_a - xz + n7;
@@ -319,7 +351,7 @@ __device__ __forceinline__ void to_raw(const R v[9], R m[9])
     m[0] = v[0] + axis + diag;
     m[1] = (v[1] - v[3]) + (d56 - d78);
     m[2] = (v[2] - v[4]) + (up - dn);
-    m[3] = axis + (R)2 * diag;
+    m[3] = fma_up((R)2, diag, axis);
     m[4] = (v[1] + v[3]) - (v[2] + v[4]);
     m[5] = d56 + d78;
     m[6] = up - dn;
@@ -356,15 +388,75 @@ __device__ __forceinline__ void relax(R m[9], const R s[9], const R meq[9], cons
         m[a] = m[a] - s[a] * (m[a] - meq[a]) + ((R)1 - (R)0.5 * s[a]) * src[a];
 }
 
+// What the collision form MODE takes of a node's populations: all of them, or
+// with every free rate 1 the moments whose rates differ from 1 (a moment
+// relaxed with rate 1 becomes its equilibrium plus half its source whatever
+// its value).  Kernels that hold rows back hold these.
+template <int MODE, typename R>
+struct Pre {
+    static constexpr int NF = 9, NG = 9;
+    R f[9], g[9];
+    __device__ __forceinline__ void take_f(const R v[9])
+    {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) f[i] = v[i];
+    }
+    __device__ __forceinline__ void take_g(const R v[9])
+    {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) g[i] = v[i];
+    }
+    __device__ __forceinline__ R mass() const { return sum9(f); }
+    __device__ __forceinline__ GSums<R> sums() const { return g_sums(g); }
+};
+template <typename R>
+struct Pre<COLLIDE_MRT_UNIT, R> {
+    static constexpr int NF = 5, NG = 6;
+    R f[5];      // mass, m3..m6
+    R g[6];      // moving sum, jz, jr, m1, m7, m8
+    __device__ __forceinline__ void take_f(const R v[9])
+    {
+        const R d13 = v[1] - v[3], d24 = v[2] - v[4];
+        const R qz = (v[5] - v[6]) - (v[7] - v[8]);
+        const R qr = (v[5] + v[6]) - (v[7] + v[8]);
+        f[0] = sum9(v);
+        f[1] = d13 + qz;
+        f[2] = fma_up((R)-2, d13, qz);
+        f[3] = d24 + qr;
+        f[4] = fma_up((R)-2, d24, qr);
+    }
+    __device__ __forceinline__ void take_g(const R v[9])
+    {
+        const GSums<R> s = g_sums(v);
+        const R axis = (v[1] + v[2]) + (v[3] + v[4]), diag = (v[5] + v[6]) + (v[7] + v[8]);
+        g[0] = s.moving;
+        g[1] = s.jz;
+        g[2] = s.jr;
+        g[3] = fma_up((R)2, diag, fma_up((R)-4, v[0], -axis));
+        g[4] = (v[1] - v[2]) + (v[3] - v[4]);
+        g[5] = (v[5] - v[6]) + (v[7] - v[8]);
+    }
+    __device__ __forceinline__ R mass() const { return f[0]; }
+    __device__ __forceinline__ GSums<R> sums() const { return GSums<R>{g[0], g[1], g[2]}; }
+};
+
 // Collision of both populations at one node (Eqs. 19, 21-23 for f; 24, 27-30,
-// 36-37 for g).  fv, gv: post-propagation values in, post-collision out.
+// 36-37 for g).  pre: what the form takes of the post-propagation values
+// (Pre); fv, gv: post-collision values out.
 // MODE selects the form (COLLIDE_*, Phys::mode); it is a template argument so
 // that each kernel holds one collision form only and the register allocation
 // is not the union of several.
 template <int MODE, typename R>
-__device__ __forceinline__ void collide_node(const Phys<R> &P, R r, R ir, const Macro<R> &m,
-                                             R php, R uzp, R urp, R fv[9], R gv[9])
+__device__ __forceinline__ void collide_pre(const Phys<R> &P, R r, R ir, const Macro<R> &m,
+                                            R php, R uzp, R urp, const Pre<MODE, R> &pre, R fv[9], R gv[9])
 {
+    if constexpr (MODE != COLLIDE_MRT_UNIT) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            fv[i] = pre.f[i];
+            gv[i] = pre.g[i];
+        }
+    }
     // ---- f (phase field)
     R rphi = r * m.phi;                          // r phi for the fluxes
     R Jz = rphi * m.uz;
@@ -374,10 +466,11 @@ __device__ __forceinline__ void collide_node(const Phys<R> &P, R r, R ir, const 
     R lam = P.lam4W * m.phi * ((R)1 - m.phi);
     R gsq = m.dz * m.dz + m.dr * m.dr;
     R nz = 0, nr = 0;
-    if (gsq > (R)1e-24) {                       // |grad phi| > 1e-12
+    const bool front = gsq > (R)1e-24;          // |grad phi| > 1e-12
+    if (__ballot(front)) {                      // of any lane: no change of the lanes at work
         R ig = rsqrt_r(gsq);
-        nz = m.dz * ig;
-        nr = m.dr * ig;
+        nz = front ? m.dz * ig : (R)0;
+        nr = front ? m.dr * ig : (R)0;
     }
     R src1 = (Jz - Jz_p) + (R)(1.0 / 3.0) * r * nz * lam;
     R src2 = (Jr - Jr_p) + (R)(1.0 / 3.0) * r * nr * lam;
@@ -387,6 +480,7 @@ __device__ __forceinline__ void collide_node(const Phys<R> &P, R r, R ir, const 
     R dzr = r * P.drho * m.dz;                 // d_z (r rho)
     R drr = r * P.drho * m.dr + rho;           // d_r (r rho)
     R Fz = r * (m.fsz + m.gzf);
+    R rur = rho * ur;
     R Fr = r * m.fsr + m.p - (R)2 * rho * m.nu * ur * ir;
     R rrho = r * rho;
     R udr = uz * dzr + ur * drr;               // u . grad(r rho)
@@ -410,9 +504,9 @@ __device__ __forceinline__ void collide_node(const Phys<R> &P, R r, R ir, const 
         {
             R s = m.s_nu, h = (R)1 - (R)0.5 * s, a = (R)1 - s;
             R q[9], w[9];
-            q[0] = h * (udr - rho * ur);
-            q[1] = s * ((R)3 * r * ((R)2 * m.p + rho * u2)) + h * ((R)2 * rho * ur);
-            q[2] = s * ((R)-3 * r * ((R)3 * m.p + rho * u2)) + h * (-udr - rho * ur);
+            q[0] = h * (udr - rur);
+            q[1] = s * ((R)3 * r * fma_up((R)2, m.p, rho * u2)) + h * ((R)2 * rho * ur);
+            q[2] = s * ((R)-3 * r * ((R)3 * m.p + rho * u2)) + h * (-udr - rur);
             q[3] = s * (rrho * uz) + h * Fz;
             q[4] = -q[3];
             q[5] = s * (rrho * ur) + h * Fr;
@@ -453,13 +547,12 @@ __device__ __forceinline__ void collide_node(const Phys<R> &P, R r, R ir, const 
             to_raw(gv, mm);
             R rp = r * m.p, ru2 = rrho * u2;
             meq[0] = 0; meq[1] = rrho * uz; meq[2] = rrho * ur;
-            meq[3] = (R)2 * rp + ru2;
+            meq[3] = fma_up((R)2, rp, ru2);
             meq[4] = rrho * (uz * uz - ur * ur);
             meq[5] = rrho * uz * ur;
             meq[6] = (R)(1.0 / 3.0) * (rrho * ur);
             meq[7] = (R)(1.0 / 3.0) * (rrho * uz);
             meq[8] = (R)(1.0 / 3.0) * (rp + ru2);
-            R rur = rho * ur;
             srcv[0] = udr - rur;
             srcv[1] = Fz; srcv[2] = Fr;
             srcv[3] = (R)(4.0 / 3.0) * udr - (R)(2.0 / 3.0) * rur;
@@ -476,17 +569,12 @@ __device__ __forceinline__ void collide_node(const Phys<R> &P, R r, R ir, const 
         return;
     }
     if constexpr (MODE == COLLIDE_MRT_UNIT) {
-        // Every free rate is 1: a moment relaxed with rate 1 becomes its
-        // equilibrium plus half its source whatever its value, so only the
-        // moments with other rates are formed from the populations:
-        // m3..m6 (rate 1/tau_f) of f, m1, m7, m8 (rate 1/tau_g) of g.
+        // Every free rate is 1: only the moments with other rates are formed
+        // from the populations: m3..m6 (rate 1/tau_f) of f, m1, m7, m8 (rate
+        // 1/tau_g) of g (Pre).
         {
-            R mass = sum9(fv);                 // conserved: sum f+ = sum f
-            R d13 = fv[1] - fv[3], d24 = fv[2] - fv[4];
-            R qz = (fv[5] - fv[6]) - (fv[7] - fv[8]);
-            R qr = (fv[5] + fv[6]) - (fv[7] + fv[8]);
-            R m3 = d13 + qz, m4 = (R)-2 * d13 + qz;
-            R m5 = d24 + qr, m6 = (R)-2 * d24 + qr;
+            R mass = pre.f[0];                 // conserved: sum f+ = sum f
+            R m3 = pre.f[1], m4 = pre.f[2], m5 = pre.f[3], m6 = pre.f[4];
             R s = P.sf[3], h = (R)1 - (R)0.5 * s;
             m3 = m3 - s * (m3 - Jz) + h * src1;
             m4 = m4 - s * (m4 + Jz) - h * src1;
@@ -497,7 +585,7 @@ __device__ __forceinline__ void collide_node(const Phys<R> &P, R r, R ir, const 
             R base_d = mass * (R)(1.0 / 36.0);
             R n3 = m3 * (R)(1.0 / 6.0), n4 = m4 * (R)(1.0 / 12.0);
             R n5 = m5 * (R)(1.0 / 6.0), n6 = m6 * (R)(1.0 / 12.0);
-            R xz = n3 - (R)2 * n4, xr = n5 - (R)2 * n6, yz = n3 + n4, yr = n5 + n6;
+            R xz = fma_up((R)-2, n4, n3), xr = fma_up((R)-2, n6, n5), yz = n3 + n4, yr = n5 + n6;
             fv[1] = base_a + xz;
             fv[2] = base_a + xr;
             fv[3] = base_a - xz;
@@ -509,19 +597,15 @@ __device__ __forceinline__ void collide_node(const Phys<R> &P, R r, R ir, const 
             fv[0] = mass - ((((fv[1] + fv[2]) + (fv[3] + fv[4])) + ((fv[5] + fv[6]) + (fv[7] + fv[8]))));
         }
         {
-            R axis = (gv[1] + gv[2]) + (gv[3] + gv[4]);
-            R diag = (gv[5] + gv[6]) + (gv[7] + gv[8]);
-            R mm[9];
-            R m1 = (R)-4 * gv[0] - axis + (R)2 * diag;
-            R m7 = (gv[1] - gv[2]) + (gv[3] - gv[4]);
-            R m8 = (gv[5] - gv[6]) + (gv[7] - gv[8]);
+            R m1 = pre.g[3], m7 = pre.g[4], m8 = pre.g[5];
             R s = m.s_nu, h = (R)1 - (R)0.5 * s;
-            R meq1 = (R)3 * r * ((R)2 * m.p + rho * u2);
+            R meq1 = (R)3 * r * fma_up((R)2, m.p, rho * u2);
             R meq7 = rrho * (uz * uz - ur * ur);
             R meq8 = rrho * uz * ur;
-            mm[0] = (R)0.5 * (udr - rho * ur);
+            R mm[9];
+            mm[0] = (R)0.5 * (udr - rur);
             mm[1] = m1 - s * (m1 - meq1) + h * ((R)2 * rho * ur);
-            mm[2] = (R)-3 * r * ((R)3 * m.p + rho * u2) + (R)0.5 * (-udr - rho * ur);
+            mm[2] = (R)-3 * r * ((R)3 * m.p + rho * u2) + (R)0.5 * (-udr - rur);
             mm[3] = rrho * uz + (R)0.5 * Fz;
             mm[4] = -mm[3];
             mm[5] = rrho * ur + (R)0.5 * Fr;
@@ -552,15 +636,15 @@ __device__ __forceinline__ void collide_node(const Phys<R> &P, R r, R ir, const 
         R mm[9], meq[9], srcv[9], s[9];
         to_moments(gv, mm);
         meq[0] = 0;
-        meq[1] = (R)3 * r * ((R)2 * m.p + rho * u2);
+        meq[1] = (R)3 * r * fma_up((R)2, m.p, rho * u2);
         meq[2] = (R)-3 * r * ((R)3 * m.p + rho * u2);
         meq[3] = rrho * uz; meq[4] = -rrho * uz;
         meq[5] = rrho * ur; meq[6] = -rrho * ur;
         meq[7] = rrho * (uz * uz - ur * ur);
         meq[8] = rrho * uz * ur;
-        srcv[0] = udr - rho * ur;                  // = r u . grad rho
+        srcv[0] = udr - rur;                       // = r u . grad rho
         srcv[1] = (R)2 * rho * ur;
-        srcv[2] = -udr - rho * ur;
+        srcv[2] = -udr - rur;
         srcv[3] = Fz; srcv[4] = -Fz; srcv[5] = Fr; srcv[6] = -Fr;
         srcv[7] = (R)(2.0 / 3.0) * (uz * dzr - ur * drr);
         srcv[8] = (R)(1.0 / 3.0) * (uz * drr + ur * dzr);
@@ -571,6 +655,17 @@ __device__ __forceinline__ void collide_node(const Phys<R> &P, R r, R ir, const 
         relax(mm, s, meq, srcv);
         from_moments(mm, gv);
     }
+}
+
+// the same from the populations: post-propagation values in, post-collision out
+template <int MODE, typename R>
+__device__ __forceinline__ void collide_node(const Phys<R> &P, R r, R ir, const Macro<R> &m,
+                                             R php, R uzp, R urp, R fv[9], R gv[9])
+{
+    Pre<MODE, R> pre;
+    pre.take_f(fv);
+    pre.take_g(gv);
+    collide_pre<MODE>(P, r, ir, m, php, uzp, urp, pre, fv, gv);
 }
 
 // ------------------------------------------------------- tile scheduling --
@@ -691,14 +786,16 @@ __device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, uint32_t voff, u
     else
         return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, POL));
 }
+template <int POL = STREAM_POL>
 __device__ __forceinline__ void buf_store(float v, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
 {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)voff, (int)soff, STREAM_POL);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)voff, (int)soff, POL);
 }
+template <int POL = STREAM_POL>
 __device__ __forceinline__ void buf_store(double v, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
 {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)voff, (int)soff, STREAM_POL);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)voff, (int)soff, POL);
 }
 
 // Byte offsets of a node (in-grid column c, element size es) and of its
@@ -796,7 +893,7 @@ template <typename T, typename R, int TZ, int TR, int MODE>
 __device__ __forceinline__ void tile_step(const Geom &g, const Phys<R> &P, int tz, int tr,
                                           const T *__restrict__ fin, const T *__restrict__ gin,
                                           T *__restrict__ fout, T *__restrict__ gout,
-                                          T *__restrict__ aux, R (*tile)[TZ + 4])
+                                          const T *__restrict__ ain, T *__restrict__ aout, R (*tile)[TZ + 4])
 {
     constexpr int NT = TZ * TR;
     constexpr int NH = (TZ + 4) * (TR + 4) - NT;
@@ -831,7 +928,7 @@ __device__ __forceinline__ void tile_step(const Geom &g, const Phys<R> &P, int t
         const int ko = (WRAP && k >= g.nz) ? k - g.nz : k;
         const ColOff co = col_off<WRAP>((uint32_t)(j * g.nz + ko) * (uint32_t)sizeof(T), ko, g, sizeof(T));
         const Pitch pt = pitch_of<T>(g);
-        const __amdgpu_buffer_rsrc_t fr = raw_rsrc(fin), gr = raw_rsrc(gin), ar = raw_rsrc(aux);
+        const __amdgpu_buffer_rsrc_t fr = raw_rsrc(fin), gr = raw_rsrc(gin), ar = raw_rsrc(ain);
         // g and aux loads keep the default cache policy as well: the shifted
         // g pulls of a wave share their end lines with the neighbouring
         // tile's, and the non-temporal hint on them measured 1 % slower
@@ -864,7 +961,7 @@ __device__ __forceinline__ void tile_step(const Geom &g, const Phys<R> &P, int t
         // a thread beyond the grid evaluates phi at its ghost cell (Sec. 2.3)
         // and reads its own g and aux at that cell without using them
         const Pitch pt = pitch_of<T>(g);
-        const char *fb = (const char *)fin, *gb = (const char *)gin, *ab = (const char *)aux;
+        const char *fb = (const char *)fin, *gb = (const char *)gin, *ab = (const char *)ain;
         int ko = inside ? k : ghost_col(k, g.nz, g.zper);
         jo = inside ? j : ghost_row(j, g.nr);
         pull9_bc<T, R>(fb, g, pt, ko, jo, fv);
@@ -898,11 +995,11 @@ __device__ __forceinline__ void tile_step(const Geom &g, const Phys<R> &P, int t
         read_stencil<R, TZ>(tile, tx, ty, st);
         R r = (R)j + (R)0.5, ir = inv_radius<R>(j);
         Macro<R> m;
-        macro_state(P, r, ir, st, gv, uzp, urp, m);
+        macro_state<MODE>(P, r, ir, st, gv, uzp, urp, m);
         collide_node<MODE>(P, r, ir, m, php, uzp, urp, fv, gv);
         const uint32_t off = (uint32_t)n * (uint32_t)sizeof(T);
         const uint32_t pb = (uint32_t)(g.plane * (int64_t)sizeof(T));
-        const __amdgpu_buffer_rsrc_t fo = raw_rsrc(fout), go = raw_rsrc(gout), ao = raw_rsrc(aux);
+        const __amdgpu_buffer_rsrc_t fo = raw_rsrc(fout), go = raw_rsrc(gout), ao = raw_rsrc(aout);
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             buf_store((T)fv[i], fo, off, (uint32_t)i * pb);
@@ -922,9 +1019,9 @@ struct CaseDesc {
     Geom g;
     Phys<R> P;
     uint64_t pop[2][2];  // [buffer][f or g]
-    uint64_t aux;
+    uint64_t aux[2];     // [buffer] (FP16-deviation storage: all its aux planes at [0])
     int cur0;            // buffer holding the state at the start of the launch sequence
-    int pad;
+    int strips;          // of the two-step launches (pair_strip)
     int64_t t0;          // the case's time when the table was uploaded (gravity ramps)
     Codec C;             // FP16-deviation storage only
 };

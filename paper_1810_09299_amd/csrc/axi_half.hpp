@@ -620,7 +620,7 @@ __device__ __forceinline__ void tile_step_h(const Geom &g, const Phys<float> &P,
     read_stencil<float, TZ>(tile, tx, ty, st);
     const float r = (float)j + 0.5f, ir = inv_radius<float>(j);
     Macro<float> m;
-    macro_state(P, r, ir, st, gv, uzp, urp, m);
+    macro_state<MOMENTS ? FORM_OF_P : MODE>(P, r, ir, st, gv, uzp, urp, m);
     if constexpr (MOMENTS) {
         const int64_t n = (int64_t)j * g.nz + k;
         F.phi[n] = (double)m.phi;

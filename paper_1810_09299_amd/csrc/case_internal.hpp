@@ -3,9 +3,12 @@
 
 #include "axi_device.hpp"
 #include "axi_half.hpp"
+#include "axi_pair.hpp"
 #include "../../include/lbm_axi.h"
 
 #include <stddef.h>
+
+struct lbm_axi_case;
 
 namespace axi {
 
@@ -26,6 +29,8 @@ struct lbm_axi_case {
     int64_t t;
     int cur;               // ping-pong buffer holding the current state
     int tile_r;
+    int cus;               // compute units of the device
+    int pair_waves, pair_rows;  // shape of the case's own two-step launches
     int device;            // HIP device the case was initialised on
     axi::Geom geom;             // geometry of the step launch (tiles for tile_r)
     axi::Phys<double> P64;
@@ -33,8 +38,8 @@ struct lbm_axi_case {
     axi::Codec codec;      // FP16-deviation storage scales
     size_t esize;          // bytes per stored value (FP16-deviation: 2)
     void *pop[2][2];       // [buffer][f or g]
-    void *aux;
-    double *fld;
+    void *aux[2];          // [buffer]; FP16-deviation storage: all its aux planes at [0]
+    double *xfer;          // one double plane: state transfer, initial phase field
     double *part;          // per-workgroup partials of the diagnostics reductions
     lbm_axi_diag *diag;    // the diagnostics record, reduced on the device
 };
@@ -44,6 +49,17 @@ namespace axi {
 Geom geom_for(const lbm_axi_case *c, int tile_r);
 // elements between population planes of an nr x nz case
 int64_t plane_elems(int nr, int nz);
+// Shape of the two-step launches (axi_pair.hpp) over the cases of one launch:
+// workgroups of `waves` wavefronts, one for each strip of columns by each run
+// of `rows` rows.
+struct PairShape {
+    int waves, rows;
+};
+int pair_strips(int nz, int z_periodic, int waves);
+inline int pair_chunks(int nr, const PairShape &s) { return (nr + s.rows - 1) / s.rows; }
+PairShape pair_shape(const lbm_axi_case *const *cases, int n);
+// whether cases of `nodes` nodes in all are advanced two steps per launch
+bool pair_pays(int64_t nodes, int precision);
 // FP16-deviation storage: buffers of ping-pong side b, and the step from side cur
 struct HalfBuf {
     float *f0;       // f_0 plane (FP32)

@@ -4,8 +4,10 @@
 //
 // Device state of one case (caller-owned block, offsets 256-byte aligned):
 //   pop[2][2][9][plane]  ping-pong x {f, g} x populations, storage type T
-//   aux[3][plane]        previous-step phi, u_z, u_r (T), updated in place
-//   fld[5][plane]        double scratch: moments fields / state transfer
+//   aux[3][plane]        previous-step phi, u_z, u_r (T) of buffer 0
+//   fld[5][plane]        doubles: the aux of buffer 1 (T) in the first planes,
+//                        the last for state transfer; with FP16-deviation
+//                        storage (axi_half.hpp) the moments fields
 //   red[...]             double scratch for the diagnostics reductions
 // plane = nr*nz rounded up to 64 elements, plus 64; SoA, z fastest.
 //   diag                 the diagnostics record (lbm_axi_diag) reduced on the device
@@ -89,11 +91,27 @@ __global__ void init_kernel(Geom g, const double *__restrict__ phi0, T *__restri
 template <typename T, typename R, int TR, int MODE>
 __global__ __launch_bounds__(TZ *TR) void step_kernel(Geom g, Phys<R> P, const T *__restrict__ fin,
                                                       const T *__restrict__ gin, T *__restrict__ fout,
-                                                      T *__restrict__ gout, T *__restrict__ aux)
+                                                      T *__restrict__ gout, const T *__restrict__ ain,
+                                                      T *__restrict__ aout)
 {
     __shared__ R tile[TR + 4][TZ + 4];
     const int t = xcd_tile(blockIdx.x, gridDim.x);
-    tile_step<T, R, TZ, TR, MODE>(g, P, t % g.tiles_z, t / g.tiles_z, fin, gin, fout, gout, aux, tile);
+    tile_step<T, R, TZ, TR, MODE>(g, P, t % g.tiles_z, t / g.tiles_z, fin, gin, fout, gout, ain, aout, tile);
+}
+
+// Two time steps of every node (pair_strip): a workgroup of blockDim / 64
+// wavefronts takes one of `strips` strips of columns by a run of `rows` rows.
+template <typename T, typename R, int MODE>
+__global__ __launch_bounds__(64 * PAIR_WAVES<R>) void pair_kernel(Geom g, Phys<R> P, R gz1, int strips, int rows,
+                                                               const T *__restrict__ fin, const T *__restrict__ gin,
+                                                               T *__restrict__ fout, T *__restrict__ gout,
+                                                               const T *__restrict__ ain, T *__restrict__ aout)
+{
+    extern __shared__ __align__(16) char lds[];
+    const int t = xcd_tile(blockIdx.x, gridDim.x);
+    const int s = t % strips, q = t / strips;
+    pair_strip<T, R, MODE>(g, P, gz1, (int)(blockDim.x >> 6), strips, s, q * rows,
+                           g.nr - q * rows < rows ? g.nr : (q + 1) * rows, fin, gin, ain, fout, gout, aout, lds);
 }
 
 __device__ __forceinline__ int64_t slot_rt(const Geom &g, int i, int k, int j)
@@ -458,7 +476,7 @@ __global__ __launch_bounds__(TZ *TR) void moments_kernel(Geom g, Phys<R> P, cons
             read_stencil<R, TZ>(tile, tx, ty, st);
             R r = (R)j + (R)0.5, ir = inv_radius<R>(j);
             Macro<R> m;
-            macro_state(P, r, ir, st, gv, uzp, urp, m);
+            macro_state<FORM_OF_P>(P, r, ir, st, gv, uzp, urp, m);
             F.phi[n] = (double)m.phi;
             F.rho[n] = (double)m.rho;
             F.uz[n] = (double)m.uz;
@@ -819,16 +837,16 @@ void launch_step(lbm_axi_case *c, const Phys<R> &P)
     T *gout = (T *)c->pop[c->cur ^ 1][1];
     if (P.mode == COLLIDE_MRT_UNIT)
         step_kernel<T, R, TR, COLLIDE_MRT_UNIT><<<c->geom.tiles, TZ * TR, 0, c->stream>>>(
-            c->geom, P, fin, gin, fout, gout, (T *)c->aux);
+            c->geom, P, fin, gin, fout, gout, (const T *)c->aux[c->cur], (T *)c->aux[c->cur ^ 1]);
     else if (P.mode == COLLIDE_SRT)
         step_kernel<T, R, TR, COLLIDE_SRT><<<c->geom.tiles, TZ * TR, 0, c->stream>>>(
-            c->geom, P, fin, gin, fout, gout, (T *)c->aux);
+            c->geom, P, fin, gin, fout, gout, (const T *)c->aux[c->cur], (T *)c->aux[c->cur ^ 1]);
     else if (P.mode == COLLIDE_NMRT)
         step_kernel<T, R, TR, COLLIDE_NMRT><<<c->geom.tiles, TZ * TR, 0, c->stream>>>(
-            c->geom, P, fin, gin, fout, gout, (T *)c->aux);
+            c->geom, P, fin, gin, fout, gout, (const T *)c->aux[c->cur], (T *)c->aux[c->cur ^ 1]);
     else
         step_kernel<T, R, TR, COLLIDE_MRT><<<c->geom.tiles, TZ * TR, 0, c->stream>>>(
-            c->geom, P, fin, gin, fout, gout, (T *)c->aux);
+            c->geom, P, fin, gin, fout, gout, (const T *)c->aux[c->cur], (T *)c->aux[c->cur ^ 1]);
 }
 
 template <typename T, typename R>
@@ -889,8 +907,53 @@ Phys<R> phys_at(const Phys<R> &P, int64_t t)
     return Q;
 }
 
+template <typename T, typename R>
+void launch_pair(lbm_axi_case *c, const Phys<R> &P)
+{
+    const T *fin = (const T *)c->pop[c->cur][0], *gin = (const T *)c->pop[c->cur][1];
+    T *fout = (T *)c->pop[c->cur ^ 1][0], *gout = (T *)c->pop[c->cur ^ 1][1];
+    const T *ain = (const T *)c->aux[c->cur];
+    T *aout = (T *)c->aux[c->cur ^ 1];
+    const int nw = c->pair_waves, strips = pair_strips(c->prm.nz, c->prm.z_periodic, nw);
+    const int chunks = pair_chunks(c->prm.nr, PairShape{nw, c->pair_rows});
+    const R gz1 = phys_at(P, c->t + 1).g_z;
+    const Phys<R> P0 = phys_at(P, c->t);
+    auto go = [&](auto mode) {
+        constexpr int MODE = decltype(mode)::value;
+        pair_kernel<T, R, MODE><<<strips * chunks, 64 * nw, pair_lds_bytes<R, MODE>(nw), c->stream>>>(
+            c->geom, P0, gz1, strips, c->pair_rows, fin, gin, fout, gout, ain, aout);
+    };
+    if (P.mode == COLLIDE_MRT_UNIT)
+        go(std::integral_constant<int, COLLIDE_MRT_UNIT>{});
+    else if (P.mode == COLLIDE_SRT)
+        go(std::integral_constant<int, COLLIDE_SRT>{});
+    else if (P.mode == COLLIDE_NMRT)
+        go(std::integral_constant<int, COLLIDE_NMRT>{});
+    else
+        go(std::integral_constant<int, COLLIDE_MRT>{});
+}
+
+// Whether the steps enqueued now are being recorded into a graph.  A replay
+// starts from the buffer the recording started from, so a recorded run of
+// 2 m steps has to end in that buffer: two steps per launch would not always.
+bool recording(hipStream_t stream)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+}
+
 int do_steps(lbm_axi_case *c, int64_t n)
 {
+    if (n >= 2 && pair_pays((int64_t)c->prm.nr * c->prm.nz, c->prm.precision) && !recording(c->stream)) {
+        for (; n >= 2; n -= 2) {
+            if (c->prm.precision == LBM_AXI_FP64)
+                launch_pair<double, double>(c, c->P64);
+            else
+                launch_pair<float, float>(c, c->P32);
+            c->cur ^= 1;
+            c->t += 2;
+        }
+    }
     for (int64_t s = 0; s < n; ++s) {
         if (c->prm.precision == LBM_AXI_FP64)
             launch_step_tr<double, double>(c, phys_at(c->P64, c->t));
@@ -906,11 +969,14 @@ int do_steps(lbm_axi_case *c, int64_t n)
 
 constexpr int MOM_TR = 4;
 
-// the case's double planes of the moments fields
+// the double planes of the moments fields: the population buffer the next
+// step writes (between steps it holds nothing that is still needed; 72 or 144
+// bytes per node against 40), with FP16-deviation storage, whose buffers are
+// smaller, planes of their own
 Fields case_fields(const lbm_axi_case *c)
 {
     const int64_t pl = c->geom.plane;
-    double *f = c->fld;
+    double *f = c->prm.precision == LBM_AXI_FP16D ? c->xfer - 4 * pl : (double *)c->pop[c->cur ^ 1][0];
     return Fields{f, f + pl, f + 2 * pl, f + 3 * pl, f + 4 * pl};
 }
 
@@ -926,14 +992,14 @@ int run_readback(lbm_axi_case *c, const Fields &F, double *scratch, lbm_axi_diag
     if (c->prm.precision == LBM_AXI_FP64)
         moments_kernel<double, double, MOM_TR><<<nb, TZ * MOM_TR, 0, c->stream>>>(
             g, phys_at(c->P64, c->t), (const double *)c->pop[c->cur][0], (const double *)c->pop[c->cur][1],
-            (const double *)c->aux, F, gas, scratch);
+            (const double *)c->aux[c->cur], F, gas, scratch);
     else if (c->prm.precision == LBM_AXI_FP16D)
         moments_kernel_h<MOM_TR><<<nb, TZ * MOM_TR, 0, c->stream>>>(g, phys_at(c->P32, c->t), c->codec,
                                                                     half_state(c, c->cur), F, gas, scratch);
     else
         moments_kernel<float, float, MOM_TR><<<nb, TZ * MOM_TR, 0, c->stream>>>(
             g, phys_at(c->P32, c->t), (const float *)c->pop[c->cur][0], (const float *)c->pop[c->cur][1],
-            (const float *)c->aux, F, gas, scratch);
+            (const float *)c->aux[c->cur], F, gas, scratch);
     const int64_t nn = (int64_t)g.nr * g.nz;
     const int np = (int)std::min<int64_t>(PRS_BLOCKS, (nn + DIAG_THREADS - 1) / DIAG_THREADS);
     diag_pressure<<<np, DIAG_THREADS, 0, c->stream>>>(g, gas, c->prm.W, F, nb, scratch);
@@ -946,6 +1012,77 @@ unsigned blocks_for(int64_t n, int threads) { return (unsigned)((n + threads - 1
 } // namespace
 
 namespace axi {
+int pair_strips(int nz, int z_periodic, int waves)
+{
+    const int lanes = 64 * waves, inner = lanes - 2 * PAIR_HALO;
+    if (z_periodic ? nz == lanes : nz <= lanes) return 1;
+    return (nz + inner - 1) / inner;
+}
+
+// The workgroup with the fewest lanes over all strips (lanes that only hold a
+// halo cost what the others do: 64 cases of 512 columns in FP32, two steps,
+// 155.8 us a step in one strip of 8 wavefronts, 167 in three of 3, 219 in ten
+// of 1; strips that share lines cost 3 % more), the smallest of equals; then the shortest runs of rows that fill the
+// device's resident wavefronts once (or the fewest times), a run costing about
+// 10 rows more than it owns: its start and the rows recomputed at its ends
+// (512 x 2048 in FP32: runs of 8 rows 30.8 us a step, of 12 31.2, of 32 over
+// 35; the 64 cases: 4 runs 155.8, 6 runs 185, 8 runs 164.8).
+PairShape pair_shape(const lbm_axi_case *const *cases, int n)
+{
+    const bool fp64 = cases[0]->prm.precision == LBM_AXI_FP64, unit = cases[0]->P64.mode == COLLIDE_MRT_UNIT;
+    // resident wavefronts per compute unit, by LDS (FP64: more than one per
+    // SIMD measured no faster, and unevenly filled SIMDs slower)
+    const int resident = fp64 ? 4 : (unit ? 12 : 8), most = fp64 ? PAIR_WAVES<double> : PAIR_WAVES<float>;
+    PairShape best{1, 0};
+    int64_t best_lanes = 0;
+    int max_nr = 0;
+    for (int i = 0; i < n; ++i) max_nr = std::max(max_nr, cases[i]->prm.nr);
+    for (int w = 1; w <= most; ++w) {
+        if (resident % w && w != 8) continue;
+        int64_t lanes = 0;
+        for (int i = 0; i < n; ++i) {
+            const lbm_axi_params &p = cases[i]->prm;
+            const int strips = pair_strips(p.nz, p.z_periodic, w);
+            // lanes counted in 33rds, strips whose edges share lines one more
+            const bool whole = pair_inner(p.nz, p.z_periodic, w, strips, fp64 ? 8 : 16) % (fp64 ? 8 : 16) == 0;
+            lanes += (int64_t)p.nr * 64 * w * strips * (whole || strips == 1 ? 32 : 33);
+        }
+        if (!best_lanes || lanes < best_lanes) {
+            best_lanes = lanes;
+            best.waves = w;
+        }
+    }
+    const int64_t slots = (int64_t)cases[0]->cus * (resident / best.waves);
+    int64_t best_cost = 0;
+    int last = 0;
+    for (int c = 1; c <= 256; ++c) {
+        const int rows = std::max(4, (max_nr + c - 1) / c);
+        if (rows == last) continue;
+        last = rows;
+        int64_t groups = 0;
+        for (int i = 0; i < n; ++i)
+            groups += (int64_t)pair_strips(cases[i]->prm.nz, cases[i]->prm.z_periodic, best.waves) *
+                      pair_chunks(cases[i]->prm.nr, PairShape{best.waves, rows});
+        const int64_t cost = (groups + slots - 1) / slots * (rows + 10);
+        if (!best_cost || cost < best_cost) {
+            best_cost = cost;
+            best.rows = rows;
+        }
+    }
+    return best;
+}
+
+// Below this a launch is too short for the strips' serial march over rows
+// (FP32, one case: 512 x 1024 22 us a step against 17.6 in single steps,
+// 512 x 2048 29 against 37.5; FP64: 128 x 2048 23 against 16.8, 512 x 2048 57
+// against 68).  FP16-deviation storage stays with single steps: encoding and
+// decoding bound it, not the traffic.
+bool pair_pays(int64_t nodes, int precision)
+{
+    if (precision == LBM_AXI_FP16D) return false;
+    return nodes >= 700000;
+}
+
 HalfBuf half_buf(const lbm_axi_case *c, int b)
 {
     const int64_t pl = c->geom.plane;
@@ -954,7 +1091,7 @@ HalfBuf half_buf(const lbm_axi_case *c, int b)
     B.f = (half_t *)((char *)c->pop[b][0] + pl * 4);
     B.g = (half_t *)c->pop[b][1];
     // aux planes: phase field of side 0, u_z, u_r, phase field of side 1
-    B.phi = (float *)c->aux + (b ? 3 * pl : 0);
+    B.phi = (float *)c->aux[0] + (b ? 3 * pl : 0);
     return B;
 }
 
@@ -970,8 +1107,8 @@ HalfState half_state(const lbm_axi_case *c, int cur)
     S.fout = out.f;
     S.gout = out.g;
     S.phout = out.phi;
-    S.uz = (float *)c->aux + c->geom.plane;
-    S.ur = (float *)c->aux + 2 * c->geom.plane;
+    S.uz = (float *)c->aux[0] + c->geom.plane;
+    S.ur = (float *)c->aux[0] + 2 * c->geom.plane;
     return S;
 }
 
@@ -1040,30 +1177,36 @@ int lbm_axi_init(const lbm_axi_params *params, void *dev_state, size_t dev_bytes
     for (int b = 0; b < 2; ++b)
         for (int q = 0; q < 2; ++q)
             c->pop[b][q] = c->base + L.off_pop + (size_t)b * (L.fbytes + L.gbytes) + (size_t)q * L.fbytes;
-    c->aux = c->base + L.off_aux;
-    c->fld = (double *)(c->base + L.off_fld);
+    c->aux[0] = c->base + L.off_aux;
+    c->aux[1] = params->precision == LBM_AXI_FP16D ? nullptr : (void *)(c->base + L.off_fld);
+    c->xfer = (double *)(c->base + L.off_fld) + 4 * L.plane;
     c->part = (double *)(c->base + L.off_part);
     c->diag = (lbm_axi_diag *)(c->base + L.off_diag);
     c->P64 = make_phys<double>(params);
     c->P32 = make_phys<float>(params);
     c->codec = make_codec(params);
     c->geom = geom_for(c, c->tile_r);
+    c->cus = 256;
+    (void)hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev);
+    const PairShape shape = pair_shape(&c, 1);
+    c->pair_waves = shape.waves;
+    c->pair_rows = shape.rows;
 
     int64_t nn = (int64_t)params->nr * params->nz;
-    if (hipMemcpyAsync(c->fld, phi0_host, nn * sizeof(double), hipMemcpyHostToDevice, c->stream) != hipSuccess) {
+    if (hipMemcpyAsync(c->xfer, phi0_host, nn * sizeof(double), hipMemcpyHostToDevice, c->stream) != hipSuccess) {
         delete c;
         return LBM_AXI_EDEVICE;
     }
     if (params->precision == LBM_AXI_FP64)
         init_kernel<double><<<blocks_for(nn, 256), 256, 0, c->stream>>>(
-            c->geom, c->fld, (double *)c->pop[0][0], (double *)c->pop[0][1], (double *)c->aux);
+            c->geom, c->xfer, (double *)c->pop[0][0], (double *)c->pop[0][1], (double *)c->aux[0]);
     else if (params->precision == LBM_AXI_FP16D)
-        init_kernel_h<<<blocks_for(nn, 256), 256, 0, c->stream>>>(c->geom, c->codec, c->fld, half_buf(c, 0),
-                                                                   (float *)c->aux + c->geom.plane,
-                                                                   (float *)c->aux + 2 * c->geom.plane);
+        init_kernel_h<<<blocks_for(nn, 256), 256, 0, c->stream>>>(c->geom, c->codec, c->xfer, half_buf(c, 0),
+                                                                   (float *)c->aux[0] + c->geom.plane,
+                                                                   (float *)c->aux[0] + 2 * c->geom.plane);
     else
         init_kernel<float><<<blocks_for(nn, 256), 256, 0, c->stream>>>(
-            c->geom, c->fld, (float *)c->pop[0][0], (float *)c->pop[0][1], (float *)c->aux);
+            c->geom, c->xfer, (float *)c->pop[0][0], (float *)c->pop[0][1], (float *)c->aux[0]);
     if (launch_ok() != LBM_AXI_OK || hipStreamSynchronize(c->stream) != hipSuccess) {
         delete c;
         return LBM_AXI_EDEVICE;
@@ -1123,13 +1266,13 @@ int lbm_axi_get_state(lbm_axi_case *c, double *f, double *g, double *aux, int64_
         if (!outs[q]) continue;
         for (int i = 0; i < 9; ++i) {
             if (half)
-                gather_plane_h<<<nb, 256, 0, c->stream>>>(G, c->codec, half_buf(c, c->cur), i, q, c->fld);
+                gather_plane_h<<<nb, 256, 0, c->stream>>>(G, c->codec, half_buf(c, c->cur), i, q, c->xfer);
             else if (c->prm.precision == LBM_AXI_FP64)
-                gather_plane_kernel<double><<<nb, 256, 0, c->stream>>>(G, i, (const double *)c->pop[c->cur][q], c->fld);
+                gather_plane_kernel<double><<<nb, 256, 0, c->stream>>>(G, i, (const double *)c->pop[c->cur][q], c->xfer);
             else
-                gather_plane_kernel<float><<<nb, 256, 0, c->stream>>>(G, i, (const float *)c->pop[c->cur][q], c->fld);
+                gather_plane_kernel<float><<<nb, 256, 0, c->stream>>>(G, i, (const float *)c->pop[c->cur][q], c->xfer);
             if (launch_ok()) return LBM_AXI_EDEVICE;
-            HIP_OK(hipMemcpyAsync(outs[q] + i * nn, c->fld, nn * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+            HIP_OK(hipMemcpyAsync(outs[q] + i * nn, c->xfer, nn * sizeof(double), hipMemcpyDeviceToHost, c->stream));
             HIP_OK(hipStreamSynchronize(c->stream));
         }
     }
@@ -1137,13 +1280,13 @@ int lbm_axi_get_state(lbm_axi_case *c, double *f, double *g, double *aux, int64_
         for (int q = 0; q < 3; ++q) {
             if (half)
                 convert_kernel<float, double><<<nb, 256, 0, c->stream>>>(
-                    nn, q == 0 ? half_buf(c, c->cur).phi : (const float *)c->aux + q * G.plane, c->fld);
+                    nn, q == 0 ? half_buf(c, c->cur).phi : (const float *)c->aux[0] + q * G.plane, c->xfer);
             else if (c->prm.precision == LBM_AXI_FP64)
-                convert_kernel<double, double><<<nb, 256, 0, c->stream>>>(nn, (const double *)c->aux + q * G.plane, c->fld);
+                convert_kernel<double, double><<<nb, 256, 0, c->stream>>>(nn, (const double *)c->aux[c->cur] + q * G.plane, c->xfer);
             else
-                convert_kernel<float, double><<<nb, 256, 0, c->stream>>>(nn, (const float *)c->aux + q * G.plane, c->fld);
+                convert_kernel<float, double><<<nb, 256, 0, c->stream>>>(nn, (const float *)c->aux[c->cur] + q * G.plane, c->xfer);
             if (launch_ok()) return LBM_AXI_EDEVICE;
-            HIP_OK(hipMemcpyAsync(aux + q * nn, c->fld, nn * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+            HIP_OK(hipMemcpyAsync(aux + q * nn, c->xfer, nn * sizeof(double), hipMemcpyDeviceToHost, c->stream));
             HIP_OK(hipStreamSynchronize(c->stream));
         }
     }
@@ -1162,9 +1305,9 @@ int lbm_axi_set_state(lbm_axi_case *c, const double *f, const double *g, const d
     if (half) {
         // the stored phase field first: FP16 f values are encoded against it
         for (int q = 0; q < 3; ++q) {
-            HIP_OK(hipMemcpyAsync(c->fld, aux + q * nn, nn * sizeof(double), hipMemcpyHostToDevice, c->stream));
+            HIP_OK(hipMemcpyAsync(c->xfer, aux + q * nn, nn * sizeof(double), hipMemcpyHostToDevice, c->stream));
             convert_kernel<double, float><<<nb, 256, 0, c->stream>>>(
-                nn, c->fld, q == 0 ? half_buf(c, c->cur).phi : (float *)c->aux + q * G.plane);
+                nn, c->xfer, q == 0 ? half_buf(c, c->cur).phi : (float *)c->aux[0] + q * G.plane);
             if (launch_ok()) return LBM_AXI_EDEVICE;
             HIP_OK(hipStreamSynchronize(c->stream));
         }
@@ -1172,22 +1315,22 @@ int lbm_axi_set_state(lbm_axi_case *c, const double *f, const double *g, const d
     const double *ins[2] = {f, g};
     for (int q = 0; q < 2; ++q)
         for (int i = 0; i < 9; ++i) {
-            HIP_OK(hipMemcpyAsync(c->fld, ins[q] + i * nn, nn * sizeof(double), hipMemcpyHostToDevice, c->stream));
+            HIP_OK(hipMemcpyAsync(c->xfer, ins[q] + i * nn, nn * sizeof(double), hipMemcpyHostToDevice, c->stream));
             if (half)
-                scatter_plane_h<<<nb, 256, 0, c->stream>>>(G, c->codec, half_buf(c, c->cur), i, q, c->fld);
+                scatter_plane_h<<<nb, 256, 0, c->stream>>>(G, c->codec, half_buf(c, c->cur), i, q, c->xfer);
             else if (c->prm.precision == LBM_AXI_FP64)
-                scatter_plane_kernel<double><<<nb, 256, 0, c->stream>>>(G, i, c->fld, (double *)c->pop[c->cur][q]);
+                scatter_plane_kernel<double><<<nb, 256, 0, c->stream>>>(G, i, c->xfer, (double *)c->pop[c->cur][q]);
             else
-                scatter_plane_kernel<float><<<nb, 256, 0, c->stream>>>(G, i, c->fld, (float *)c->pop[c->cur][q]);
+                scatter_plane_kernel<float><<<nb, 256, 0, c->stream>>>(G, i, c->xfer, (float *)c->pop[c->cur][q]);
             if (launch_ok()) return LBM_AXI_EDEVICE;
             HIP_OK(hipStreamSynchronize(c->stream));
         }
     for (int q = 0; q < 3 && !half; ++q) {
-        HIP_OK(hipMemcpyAsync(c->fld, aux + q * nn, nn * sizeof(double), hipMemcpyHostToDevice, c->stream));
+        HIP_OK(hipMemcpyAsync(c->xfer, aux + q * nn, nn * sizeof(double), hipMemcpyHostToDevice, c->stream));
         if (c->prm.precision == LBM_AXI_FP64)
-            convert_kernel<double, double><<<nb, 256, 0, c->stream>>>(nn, c->fld, (double *)c->aux + q * G.plane);
+            convert_kernel<double, double><<<nb, 256, 0, c->stream>>>(nn, c->xfer, (double *)c->aux[c->cur] + q * G.plane);
         else
-            convert_kernel<double, float><<<nb, 256, 0, c->stream>>>(nn, c->fld, (float *)c->aux + q * G.plane);
+            convert_kernel<double, float><<<nb, 256, 0, c->stream>>>(nn, c->xfer, (float *)c->aux[c->cur] + q * G.plane);
         if (launch_ok()) return LBM_AXI_EDEVICE;
         HIP_OK(hipStreamSynchronize(c->stream));
     }

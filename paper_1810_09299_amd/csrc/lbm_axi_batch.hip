@@ -74,7 +74,8 @@ __global__ __launch_bounds__(TZ *TR) void batch_step_kernel(char *__restrict__ p
         int cur = d.cur0 ^ parity;
         tile_step<T, R, TZ, TR, MODE>(d.g, phys_of(d, step), it.tz, it.tr, (const T *)(pool + d.pop[cur][0]),
                                       (const T *)(pool + d.pop[cur][1]), (T *)(pool + d.pop[cur ^ 1][0]),
-                                      (T *)(pool + d.pop[cur ^ 1][1]), (T *)(pool + d.aux), tile);
+                                      (T *)(pool + d.pop[cur ^ 1][1]), (const T *)(pool + d.aux[cur]),
+                                      (T *)(pool + d.aux[cur ^ 1]), tile);
         __syncthreads();
     }
 }
@@ -115,7 +116,7 @@ __global__ __launch_bounds__(TZ *TR) __attribute__((amdgpu_waves_per_eu(
             P.round_key = mix32((uint32_t)tn);
         }
         const size_t pb4 = (size_t)d.g.plane * 4;
-        char *aux = pool + d.aux;
+        char *aux = pool + d.aux[0];
         HalfState S;
         S.f0in = (const float *)(pool + d.pop[cur][0]);
         S.fin = (const half_t *)(pool + d.pop[cur][0] + pb4);
@@ -130,6 +131,26 @@ __global__ __launch_bounds__(TZ *TR) __attribute__((amdgpu_waves_per_eu(
         tile_step_h<TZ, TR, MODE, false, SR>(d.g, P, d.C, it.tz, it.tr, S, Fields{}, tile);
         __syncthreads();
     }
+}
+
+// Two steps of every work item (pair_strip): item = (slot, strip, first row,
+// rows).
+template <typename T, typename R, int MODE>
+__global__ __launch_bounds__(64 * PAIR_WAVES<R>) void batch_pair_kernel(char *__restrict__ pool,
+                                                                     const CaseDesc<R> *__restrict__ descs,
+                                                                     const WorkItem *__restrict__ work, int parity,
+                                                                     int step)
+{
+    extern __shared__ __align__(16) char lds[];
+    const WorkItem it = work[blockIdx.x];
+    if (it.slot < 0) return;
+    const CaseDesc<R> &d = descs[it.slot];
+    const int cur = d.cur0 ^ parity;
+    pair_strip<T, R, MODE>(d.g, phys_of(d, step), phys_of(d, step + 1).g_z, (int)(blockDim.x >> 6), d.strips, it.tz,
+                           it.tr, it.tr + it.pad, (const T *)(pool + d.pop[cur][0]),
+                           (const T *)(pool + d.pop[cur][1]), (const T *)(pool + d.aux[cur]),
+                           (T *)(pool + d.pop[cur ^ 1][0]), (T *)(pool + d.pop[cur ^ 1][1]),
+                           (T *)(pool + d.aux[cur ^ 1]), lds);
 }
 
 struct Block {
@@ -196,6 +217,9 @@ struct lbm_axi_batch {
     std::vector<hipEvent_t> done_ev;    // recorded after a case's last step
     // current launch configuration
     std::vector<WorkItem> work;         // grouped by collision form
+    std::vector<WorkItem> pair_work;    // items of the two-step launches, after `work` on the device (empty: none)
+    int pair_start[NMODE + 1];
+    int pair_waves[NMODE];              // wavefronts of their workgroups, per collision form
     int mode_start[NCLASS + 1];         // items of class q: [mode_start[q], mode_start[q + 1])
     std::vector<int> running;           // slots in the work list
     bool dirty;                         // work list / descriptors must be rebuilt
@@ -347,9 +371,10 @@ CaseDesc<R> make_desc(const lbm_axi_batch *b, const lbm_axi_case *c, const Phys<
     for (int q = 0; q < 2; ++q)
         for (int s = 0; s < 2; ++s)
             d.pop[q][s] = (uint64_t)((char *)c->pop[q][s] - b->pool);
-    d.aux = (uint64_t)((char *)c->aux - b->pool);
+    for (int q = 0; q < 2; ++q)
+        d.aux[q] = c->aux[q] ? (uint64_t)((char *)c->aux[q] - b->pool) : 0;
     d.cur0 = c->cur ^ b->phase;
-    d.pad = 0;
+    d.strips = pair_strips(c->prm.nz, c->prm.z_periodic, b->pair_waves[c->P64.mode]);
     d.t0 = c->t;
     d.C = c->codec;
     return d;
@@ -415,6 +440,44 @@ bool ramping_at(const lbm_axi_case *c, int64_t t)
     return c->prm.g_ramp > 0.0 && (double)(t + 1) < c->prm.g_ramp;
 }
 
+// The work lists of the two-step launches for the running cases (`order`:
+// grouped by collision form), or none.  The strips of one run of rows go to one
+// XCD (they share the lines at their edges; 64 cases of 256 x 512 in FP32:
+// 185 -> 167 us a step), run after run round the XCDs: position p runs on XCD
+// p % 8.
+void build_pairs(lbm_axi_batch *b, const std::vector<int> &order)
+{
+    b->pair_work.clear();
+    for (int q = 0; q <= NMODE; ++q) b->pair_start[q] = 0;
+    int64_t nodes = 0;
+    for (int s : order) nodes += (int64_t)b->cases[s]->prm.nr * b->cases[s]->prm.nz;
+    if (!pair_pays(nodes, b->precision)) return;
+    for (size_t first = 0, end; first < order.size(); first = end) {
+        const int mode = b->cases[order[first]]->P64.mode;
+        std::vector<const lbm_axi_case *> form;
+        for (end = first; end < order.size() && b->cases[order[end]]->P64.mode == mode; ++end)
+            form.push_back(b->cases[order[end]]);
+        const PairShape shape = pair_shape(form.data(), (int)form.size());
+        b->pair_waves[mode] = shape.waves;
+        std::vector<WorkItem> queue[8];
+        int next = 0;
+        for (size_t i = 0; i < form.size(); ++i) {
+            const lbm_axi_params &p = form[i]->prm;
+            const int strips = pair_strips(p.nz, p.z_periodic, shape.waves);
+            for (int ra = 0; ra < p.nr; ra += shape.rows, next = (next + 1) % 8)
+                for (int k = 0; k < strips; ++k)
+                    queue[next].push_back(WorkItem{order[first + i], k, ra, std::min(shape.rows, p.nr - ra)});
+        }
+        size_t longest = 0;
+        for (const auto &x : queue) longest = std::max(longest, x.size());
+        for (size_t l = 0; l < longest; ++l)
+            for (const auto &x : queue) b->pair_work.push_back(l < x.size() ? x[l] : WorkItem{-1, 0, 0, 0});
+        for (int q = mode + 1; q <= NMODE; ++q) b->pair_start[q] = (int)b->pair_work.size();
+    }
+    // both lists share the reserved area
+    if (b->work.size() + b->pair_work.size() > (size_t)MAX_WORK) b->pair_work.clear();
+}
+
 // rebuild the descriptor table and work list for the running cases; the
 // upload is ordered on the stream after every step already enqueued
 int rebuild(lbm_axi_batch *b)
@@ -442,11 +505,12 @@ int rebuild(lbm_axi_batch *b)
         for (int q = launch_class(b->cases[s]) + 1; q <= NCLASS; ++q) b->mode_start[q] = (int)b->work.size();
     }
     if ((int64_t)b->work.size() > MAX_WORK) return LBM_AXI_EBUSY;   // admission keeps this from happening
+    build_pairs(b, order);
     // descriptors of every used slot, the cases' times, then the work list, in
     // one staging buffer
     const size_t ds = desc_size(b->precision);
     const size_t dbytes = ds * b->max_cases, tbytes = 2 * sizeof(int64_t) * b->max_cases;
-    const size_t wbytes = b->work.size() * sizeof(WorkItem);
+    const size_t wbytes1 = b->work.size() * sizeof(WorkItem), wbytes = wbytes1 + b->pair_work.size() * sizeof(WorkItem);
     Stage *st = stage_acquire(b, dbytes + tbytes + wbytes);
     if (!st) return LBM_AXI_EDEVICE;
     char *host = (char *)st->host;
@@ -464,7 +528,8 @@ int rebuild(lbm_axi_batch *b)
             memcpy(host + s * ds, &d, ds);
         }
     }
-    if (wbytes) memcpy(host + dbytes + tbytes, b->work.data(), wbytes);
+    if (wbytes1) memcpy(host + dbytes + tbytes, b->work.data(), wbytes1);
+    if (wbytes > wbytes1) memcpy(host + dbytes + tbytes + wbytes1, b->pair_work.data(), wbytes - wbytes1);
     if (hipMemcpyAsync(b->d_descs, host, dbytes, hipMemcpyHostToDevice, b->stream) != hipSuccess)
         return LBM_AXI_EDEVICE;
     if (hipMemcpyAsync(b->d_times, host + dbytes, tbytes, hipMemcpyHostToDevice, b->stream) != hipSuccess)
@@ -532,12 +597,42 @@ void launch_one(lbm_axi_batch *b, int parity, int step)
     }
 }
 
+template <typename T, typename R, int MODE>
+void launch_pair_part(lbm_axi_batch *b, int parity, int step)
+{
+    const int first = b->pair_start[MODE], n = b->pair_start[MODE + 1] - first;
+    if (n > 0)
+        batch_pair_kernel<T, R, MODE><<<n, 64 * b->pair_waves[MODE], pair_lds_bytes<R, MODE>(b->pair_waves[MODE]), b->stream>>>(
+            b->pool, (const CaseDesc<R> *)b->d_descs, b->d_work + b->work.size() + first, parity, step);
+}
+
+template <typename T, typename R>
+void launch_pairs(lbm_axi_batch *b, int parity, int step)
+{
+    launch_pair_part<T, R, COLLIDE_MRT>(b, parity, step);
+    launch_pair_part<T, R, COLLIDE_MRT_UNIT>(b, parity, step);
+    launch_pair_part<T, R, COLLIDE_SRT>(b, parity, step);
+    launch_pair_part<T, R, COLLIDE_NMRT>(b, parity, step);
+}
+
+// launches that n steps take: two steps each where the running cases have a
+// list for it, the odd one alone (every launch flips the buffer phase)
+int launches_of(const lbm_axi_batch *b, int n) { return b->pair_work.empty() ? n : n / 2 + (n & 1); }
+
 // n steps starting at buffer phase `phase`, the first `first` steps after the
 // table upload
 void launch_steps(lbm_axi_batch *b, int n, int phase, int64_t first)
 {
-    for (int s = 0; s < n; ++s) {
-        const int parity = (phase ^ s) & 1;
+    int parity = phase & 1;
+    int s = 0;
+    for (; !b->pair_work.empty() && s + 2 <= n; s += 2, parity ^= 1) {
+        const int step = (int)std::min<int64_t>(first + s, INT32_MAX - 1);
+        if (b->precision == LBM_AXI_FP64)
+            launch_pairs<double, double>(b, parity, step);
+        else
+            launch_pairs<float, float>(b, parity, step);
+    }
+    for (; s < n; ++s, parity ^= 1) {
         const int step = (int)std::min<int64_t>(first + s, INT32_MAX);
         if (b->precision == LBM_AXI_FP64)
             launch_one<double, double>(b, parity, step);
@@ -588,7 +683,7 @@ int run_span(lbm_axi_batch *b, int n, bool use_graph)
     b->launches += n;
     b->since_upload += n;
     // host bookkeeping: time, remaining steps, buffer of every running case
-    const int flip = n & 1;
+    const int flip = launches_of(b, n) & 1;
     b->phase ^= flip;
     bool still_ramping = false;
     for (int s : b->running) {
@@ -701,6 +796,8 @@ int lbm_axi_batch_create(void *dev_pool, size_t pool_bytes, int32_t max_cases, i
     b->done_ev.assign(max_cases, nullptr);
     b->dirty = true;
     for (int q = 0; q <= NCLASS; ++q) b->mode_start[q] = 0;
+    for (int q = 0; q <= NMODE; ++q) b->pair_start[q] = 0;
+    for (int &w : b->pair_waves) w = 1;
     b->launches = 0;
     *out = b;
     return LBM_AXI_OK;

@@ -1,0 +1,109 @@
+"""Two time steps per launch (large FP64 and FP32 cases and batches) against
+one step per launch: the same operations on every node, so the same bits."""
+import numpy as np
+import pytest
+
+from paper_1810_09299_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+PAIRED_NODES = 700_000      # nodes of a case or batch from which steps run in pairs
+
+
+def _spec(nr, nz, zper, collision):
+    s = inputs.static_droplet(nr=nr, nz=nz, R=max(2.0, 0.3 * min(nr, nz)), W=4.0, ratio=10.0, sigma=1e-3,
+                              z_periodic=zper)
+    s.collision = "mrt" if collision == "general" else collision
+    s.g_z, s.g_ramp = -1e-5, 6.0                      # each of the two steps has its own acceleration
+    if collision in ("general", "nmrt"):
+        s.s_g = (1.0, 1.1, 1.2, 1.1, 1.1, 0.9, 0.9, 1.0, 1.0)
+        s.free_s1 = True
+    return s
+
+
+def _single_steps(spec, precision, n):
+    """State after n steps taken one by one."""
+    from paper_1810_09299_amd.case import AxiCase
+    c = AxiCase(spec, precision=precision)
+    for _ in range(n):
+        c.step(1)
+    st = c.get_state()
+    c.close()
+    return st
+
+
+# widths at the edges of one and two wavefronts, of a strip's own columns, and
+# of a whole period of lanes (64, 128, 512); fewest rows, short runs of rows
+GRIDS = [(4, 4), (5, 7), (9, 54), (16, 55), (7, 64), (12, 65), (20, 118), (33, 119), (40, 128), (24, 182), (11, 247),
+         (10, 502), (13, 503), (48, 512), (6, 513)]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("collision", ["mrt", "general", "srt", "nmrt"])
+def test_batch_pairs_equal_single_steps(precision, collision):
+    """Small and odd grids, periodic and walled, beside a large one that makes
+    the batch run two steps per launch; 7 steps: three pairs and an odd step."""
+    from paper_1810_09299_amd.batch import Batch
+    specs = [_spec(nr, nz, zper, collision) for nr, nz in GRIDS for zper in (True, False)]
+    big = _spec(701, 1001, True, collision)
+    assert big.nodes > PAIRED_NODES
+    b = Batch(pool_bytes=Batch.pool_for(specs + [big], precision), max_cases=len(specs) + 1, precision=precision)
+    slots = [b.admit(s, 7) for s in specs]
+    b.admit(big, 8)
+    b.run(7)
+    for s, slot in zip(specs, slots):
+        f, g, aux, t = b.get_state(slot)
+        fs, gs, xs, ts = _single_steps(s, precision, 7)
+        assert t == ts == 7
+        assert np.isfinite(f).all() and np.isfinite(g).all()
+        assert np.array_equal(f, fs) and np.array_equal(g, gs) and np.array_equal(aux, xs), (s.nr, s.nz, s.z_periodic)
+    b.close()
+
+
+@pytest.mark.parametrize("precision,nr,nz,zper", [("fp64", 353, 2003, True), ("fp64", 1405, 500, False),
+                                                  ("fp32", 353, 2003, False), ("fp32", 1370, 512, True),
+                                                  ("fp32", 5600, 128, False)])
+def test_case_pairs_equal_single_steps(precision, nr, nz, zper):
+    """One large case: any split of the steps into calls gives the same state,
+    and reading it back (whose fields use the other population buffer) or
+    loading a state between pairs leaves the next steps right."""
+    from paper_1810_09299_amd.case import AxiCase
+    spec = _spec(nr, nz, zper, "mrt")
+    assert spec.nodes >= PAIRED_NODES
+    ref = _single_steps(spec, precision, 8)
+    c = AxiCase(spec, precision=precision)
+    c.step(5)
+    fields, _, _ = c.moments()
+    st = c.get_state()
+    assert np.array_equal(c.moments()[0]["p"], fields["p"])
+    c.step(3)
+    got = c.get_state()
+    assert got[3] == 8
+    for x, y in zip(ref[:3], got[:3]):
+        assert np.array_equal(x, y)
+    c.set_state(*st)
+    c.step(3)
+    for x, y in zip(ref[:3], c.get_state()[:3]):
+        assert np.array_equal(x, y)
+    c.close()
+
+
+def test_recorded_steps_replay_from_their_own_result():
+    """Steps recorded into a graph go one by one: an even number of them ends in
+    the buffer they started from, so replays continue each other."""
+    import torch
+    from paper_1810_09299_amd.case import AxiCase
+    spec = _spec(701, 1001, True, "mrt")
+    spec.g_ramp = 0.0                                 # a recording holds the acceleration of its own steps
+    ref = _single_steps(spec, "fp32", 6)
+    stream = torch.cuda.Stream()
+    c = AxiCase(spec, precision="fp32", stream=stream)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        c.step(2)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+    for x, y in zip(ref[:3], c.get_state()[:3]):
+        assert np.array_equal(x, y)
+    c.close()
