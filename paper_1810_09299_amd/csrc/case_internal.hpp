@@ -4,6 +4,7 @@
 #include "axi_device.hpp"
 #include "axi_half.hpp"
 #include "axi_pair.hpp"
+#include "axi_tile.hpp"
 #include "../../include/lbm_axi.h"
 
 #include <stddef.h>
@@ -18,6 +19,13 @@ constexpr int TZ = 64;          // tile width along z: one wave per tile row
 #endif
 constexpr int PLANE_PAD = AXI_PLANE_PAD;   // spare elements per population plane
 
+// How the cases of one launch advance two steps at once (FP64 and FP32).
+struct TwoStepPlan {
+    bool march;            // strips marching up the rows (axi_pair.hpp), else tiles (axi_tile.hpp)
+    int waves, rows;       // march: wavefronts of a workgroup, rows of a run
+    int tile;              // tiles: the shape (with_tile_shape)
+};
+
 } // namespace axi
 
 // One case: its geometry, rates and the pointers into its device block.
@@ -30,7 +38,7 @@ struct lbm_axi_case {
     int cur;               // ping-pong buffer holding the current state
     int tile_r;
     int cus;               // compute units of the device
-    int pair_waves, pair_rows;  // shape of the case's own two-step launches
+    axi::TwoStepPlan two;  // of the case's own launches
     int device;            // HIP device the case was initialised on
     axi::Geom geom;             // geometry of the step launch (tiles for tile_r)
     axi::Phys<double> P64;
@@ -49,17 +57,10 @@ namespace axi {
 Geom geom_for(const lbm_axi_case *c, int tile_r);
 // elements between population planes of an nr x nz case
 int64_t plane_elems(int nr, int nz);
-// Shape of the two-step launches (axi_pair.hpp) over the cases of one launch:
-// workgroups of `waves` wavefronts, one for each strip of columns by each run
-// of `rows` rows.
-struct PairShape {
-    int waves, rows;
-};
+// how many strips `waves` wavefronts cut nz columns into (axi_pair.hpp)
 int pair_strips(int nz, int z_periodic, int waves);
-inline int pair_chunks(int nr, const PairShape &s) { return (nr + s.rows - 1) / s.rows; }
-PairShape pair_shape(const lbm_axi_case *const *cases, int n);
-// whether cases of `nodes` nodes in all are advanced two steps per launch
-bool pair_pays(int64_t nodes, int precision);
+// two steps per launch for the n cases of one launch: the plan that suits them
+TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n);
 // FP16-deviation storage: buffers of ping-pong side b, and the step from side cur
 struct HalfBuf {
     float *f0;       // f_0 plane (FP32)

@@ -114,6 +114,19 @@ __global__ __launch_bounds__(64 * PAIR_WAVES<R>) void pair_kernel(Geom g, Phys<R
                            g.nr - q * rows < rows ? g.nr : (q + 1) * rows, fin, gin, ain, fout, gout, aout, lds);
 }
 
+// Two time steps of every node of a small case: one tile per workgroup
+// (tile_two_steps).
+template <typename T, typename R, int MODE, typename S>
+__global__ __launch_bounds__(S::THREADS) void tile_kernel(Geom g, Phys<R> P, R gz1, int tiles_z,
+                                                          const T *__restrict__ fin, const T *__restrict__ gin,
+                                                          T *__restrict__ fout, T *__restrict__ gout,
+                                                          const T *__restrict__ ain, T *__restrict__ aout)
+{
+    extern __shared__ __align__(16) char lds[];
+    const int b = xcd_tile(blockIdx.x, gridDim.x);
+    tile_two_steps<T, R, MODE, S>(g, P, gz1, b % tiles_z, b / tiles_z, fin, gin, ain, fout, gout, aout, (R *)lds);
+}
+
 __device__ __forceinline__ int64_t slot_rt(const Geom &g, int i, int k, int j)
 {
     switch (i) {
@@ -907,21 +920,32 @@ Phys<R> phys_at(const Phys<R> &P, int64_t t)
     return Q;
 }
 
+// two time steps in one launch
 template <typename T, typename R>
-void launch_pair(lbm_axi_case *c, const Phys<R> &P)
+void launch_two(lbm_axi_case *c, const Phys<R> &P)
 {
     const T *fin = (const T *)c->pop[c->cur][0], *gin = (const T *)c->pop[c->cur][1];
     T *fout = (T *)c->pop[c->cur ^ 1][0], *gout = (T *)c->pop[c->cur ^ 1][1];
     const T *ain = (const T *)c->aux[c->cur];
     T *aout = (T *)c->aux[c->cur ^ 1];
-    const int nw = c->pair_waves, strips = pair_strips(c->prm.nz, c->prm.z_periodic, nw);
-    const int chunks = pair_chunks(c->prm.nr, PairShape{nw, c->pair_rows});
-    const R gz1 = phys_at(P, c->t + 1).g_z;
     const Phys<R> P0 = phys_at(P, c->t);
+    const R gz1 = phys_at(P, c->t + 1).g_z;
+    const int nr = c->prm.nr, nz = c->prm.nz;
+    const TwoStepPlan &w = c->two;
     auto go = [&](auto mode) {
         constexpr int MODE = decltype(mode)::value;
-        pair_kernel<T, R, MODE><<<strips * chunks, 64 * nw, pair_lds_bytes<R, MODE>(nw), c->stream>>>(
-            c->geom, P0, gz1, strips, c->pair_rows, fin, gin, fout, gout, ain, aout);
+        if (w.march) {
+            const int strips = pair_strips(nz, c->prm.z_periodic, w.waves), runs = (nr + w.rows - 1) / w.rows;
+            pair_kernel<T, R, MODE><<<strips * runs, 64 * w.waves, pair_lds_bytes<R, MODE>(w.waves), c->stream>>>(
+                c->geom, P0, gz1, strips, w.rows, fin, gin, fout, gout, ain, aout);
+            return;
+        }
+        with_tile_shape(w.tile, [&](auto shape) {
+            using S = decltype(shape);
+            const int tiles_z = (nz + S::OZ - 1) / S::OZ, tiles = tiles_z * ((nr + S::OR - 1) / S::OR);
+            tile_kernel<T, R, MODE, S><<<tiles, S::THREADS, S::LDS_VALUES * sizeof(R), c->stream>>>(
+                c->geom, P0, gz1, tiles_z, fin, gin, fout, gout, ain, aout);
+        });
     };
     if (P.mode == COLLIDE_MRT_UNIT)
         go(std::integral_constant<int, COLLIDE_MRT_UNIT>{});
@@ -944,12 +968,12 @@ bool recording(hipStream_t stream)
 
 int do_steps(lbm_axi_case *c, int64_t n)
 {
-    if (n >= 2 && pair_pays((int64_t)c->prm.nr * c->prm.nz, c->prm.precision) && !recording(c->stream)) {
+    if (n >= 2 && c->prm.precision != LBM_AXI_FP16D && !recording(c->stream)) {
         for (; n >= 2; n -= 2) {
             if (c->prm.precision == LBM_AXI_FP64)
-                launch_pair<double, double>(c, c->P64);
+                launch_two<double, double>(c, c->P64);
             else
-                launch_pair<float, float>(c, c->P32);
+                launch_two<float, float>(c, c->P32);
             c->cur ^= 1;
             c->t += 2;
         }
@@ -1019,21 +1043,22 @@ int pair_strips(int nz, int z_periodic, int waves)
     return (nz + inner - 1) / inner;
 }
 
-// The workgroup with the fewest lanes over all strips (lanes that only hold a
-// halo cost what the others do: 64 cases of 512 columns in FP32, two steps,
-// 155.8 us a step in one strip of 8 wavefronts, 167 in three of 3, 219 in ten
-// of 1; strips that share lines cost 3 % more), the smallest of equals; then the shortest runs of rows that fill the
-// device's resident wavefronts once (or the fewest times), a run costing about
-// 10 rows more than it owns: its start and the rows recomputed at its ends
-// (512 x 2048 in FP32: runs of 8 rows 30.8 us a step, of 12 31.2, of 32 over
-// 35; the 64 cases: 4 runs 155.8, 6 runs 185, 8 runs 164.8).
-PairShape pair_shape(const lbm_axi_case *const *cases, int n)
+// The march's workgroup is the one with the fewest lanes over all strips (lanes
+// that only hold a halo cost what the others do: 64 cases of 512 columns in
+// FP32 took 155.8 us a step in one strip of 8 wavefronts, 167 in three of 3, 219
+// in ten of 1; strips that share lines cost 3 % more), the smallest of equals;
+// then the shortest runs of rows that fill the device's resident wavefronts
+// once (or the fewest times), a run costing about 10 rows more than it owns:
+// its start and the rows recomputed at its ends (512 x 2048 in FP32: runs of 8
+// rows 30.8 us a step, of 12 31.2, of 32 over 35; the 64 cases: 4 runs 155.8, 6
+// runs 185, 8 runs 164.8).
+static void plan_march(const lbm_axi_case *const *cases, int n, TwoStepPlan &best)
 {
     const bool fp64 = cases[0]->prm.precision == LBM_AXI_FP64, unit = cases[0]->P64.mode == COLLIDE_MRT_UNIT;
     // resident wavefronts per compute unit, by LDS (FP64: more than one per
     // SIMD measured no faster, and unevenly filled SIMDs slower)
     const int resident = fp64 ? 4 : (unit ? 12 : 8), most = fp64 ? PAIR_WAVES<double> : PAIR_WAVES<float>;
-    PairShape best{1, 0};
+    const int line = fp64 ? 8 : 16;
     int64_t best_lanes = 0;
     int max_nr = 0;
     for (int i = 0; i < n; ++i) max_nr = std::max(max_nr, cases[i]->prm.nr);
@@ -1043,9 +1068,8 @@ PairShape pair_shape(const lbm_axi_case *const *cases, int n)
         for (int i = 0; i < n; ++i) {
             const lbm_axi_params &p = cases[i]->prm;
             const int strips = pair_strips(p.nz, p.z_periodic, w);
-            // lanes counted in 33rds, strips whose edges share lines one more
-            const bool whole = pair_inner(p.nz, p.z_periodic, w, strips, fp64 ? 8 : 16) % (fp64 ? 8 : 16) == 0;
-            lanes += (int64_t)p.nr * 64 * w * strips * (whole || strips == 1 ? 32 : 33);
+            const bool whole = strips == 1 || pair_inner(p.nz, p.z_periodic, w, strips, line) % line == 0;
+            lanes += (int64_t)p.nr * 64 * w * strips * (whole ? 32 : 33);
         }
         if (!best_lanes || lanes < best_lanes) {
             best_lanes = lanes;
@@ -1062,25 +1086,51 @@ PairShape pair_shape(const lbm_axi_case *const *cases, int n)
         int64_t groups = 0;
         for (int i = 0; i < n; ++i)
             groups += (int64_t)pair_strips(cases[i]->prm.nz, cases[i]->prm.z_periodic, best.waves) *
-                      pair_chunks(cases[i]->prm.nr, PairShape{best.waves, rows});
+                      ((cases[i]->prm.nr + rows - 1) / rows);
         const int64_t cost = (groups + slots - 1) / slots * (rows + 10);
         if (!best_cost || cost < best_cost) {
             best_cost = cost;
             best.rows = rows;
         }
     }
-    return best;
 }
 
-// Below this a launch is too short for the strips' serial march over rows
-// (FP32, one case: 512 x 1024 22 us a step against 17.6 in single steps,
-// 512 x 2048 29 against 37.5; FP64: 128 x 2048 23 against 16.8, 512 x 2048 57
-// against 68).  FP16-deviation storage stays with single steps: encoding and
-// decoding bound it, not the traffic.
-bool pair_pays(int64_t nodes, int precision)
+// Marching takes too long to start for what fits the caches: one FP32 case of
+// 512 x 1024 21.5 us a step against 15.2 in tiles, of 512 x 2048 30 against 28,
+// 16 cases of 256 x 512 46 against 57; FP64, 512 x 1024 30 against 26, 512 x
+// 2048 51 against 59.
+// Tiles: the smallest that still gives every compute unit at most one, since
+// smaller ones are sooner done (64 x 128 FP32: 3.4 us a step in 8 x 4, 3.5 in
+// 12 x 8, 4.1 in 16 x 16; 60 x 286 FP64: 4.3 in 12 x 8, 5.5 in 16 x 16; 128 x
+// 512 FP32: 4.4 in 16 x 16, 5.8 in 32 x 16); beyond that the one with the
+// smaller share of halo, in FP64 the one of which two fit a compute unit's LDS
+// (128 x 2048: 15.8 in 16 x 16, 17.1 in 32 x 16; FP32 10.6 and 9.4).
+// Single steps took 5.2 (64 x 128, FP32, the default tile), 7.8 (60 x 286,
+// FP64), 11.1 (128 x 2048, FP32).
+TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n)
 {
-    if (precision == LBM_AXI_FP16D) return false;
-    return nodes >= 700000;
+    TwoStepPlan plan{false, 1, 4, 0};
+    const bool fp64 = cases[0]->prm.precision == LBM_AXI_FP64;
+    int64_t nodes = 0;
+    for (int i = 0; i < n; ++i) nodes += (int64_t)cases[i]->prm.nr * cases[i]->prm.nz;
+    plan.march = nodes >= (fp64 ? 800000 : 1200000);
+    if (plan.march) {
+        plan_march(cases, n, plan);
+        return plan;
+    }
+    auto groups = [&](int shape) {
+        int64_t s = 0;
+        with_tile_shape(shape, [&](auto t) {
+            using S = decltype(t);
+            for (int i = 0; i < n; ++i)
+                s += (int64_t)((cases[i]->prm.nz + S::OZ - 1) / S::OZ) * ((cases[i]->prm.nr + S::OR - 1) / S::OR);
+        });
+        return s;
+    };
+    for (plan.tile = 0; plan.tile < TILE_SHAPES; ++plan.tile)
+        if (groups(plan.tile) <= cases[0]->cus) return plan;
+    plan.tile = fp64 ? 2 : 3;
+    return plan;
 }
 
 HalfBuf half_buf(const lbm_axi_case *c, int b)
@@ -1188,9 +1238,7 @@ int lbm_axi_init(const lbm_axi_params *params, void *dev_state, size_t dev_bytes
     c->geom = geom_for(c, c->tile_r);
     c->cus = 256;
     (void)hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev);
-    const PairShape shape = pair_shape(&c, 1);
-    c->pair_waves = shape.waves;
-    c->pair_rows = shape.rows;
+    c->two = two_step_plan(&c, 1);
 
     int64_t nn = (int64_t)params->nr * params->nz;
     if (hipMemcpyAsync(c->xfer, phi0_host, nn * sizeof(double), hipMemcpyHostToDevice, c->stream) != hipSuccess) {

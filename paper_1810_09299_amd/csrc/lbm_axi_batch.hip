@@ -153,6 +153,24 @@ __global__ __launch_bounds__(64 * PAIR_WAVES<R>) void batch_pair_kernel(char *__
                            (T *)(pool + d.aux[cur ^ 1]), lds);
 }
 
+// Two steps of every work item (tile_two_steps): item = (slot, tile column,
+// tile row) of tiles of the shape S.
+template <typename T, typename R, int MODE, typename S>
+__global__ __launch_bounds__(S::THREADS) void batch_tile_kernel(char *__restrict__ pool,
+                                                                const CaseDesc<R> *__restrict__ descs,
+                                                                const WorkItem *__restrict__ work, int parity, int step)
+{
+    extern __shared__ __align__(16) char lds[];
+    const WorkItem it = work[blockIdx.x];
+    if (it.slot < 0) return;
+    const CaseDesc<R> &d = descs[it.slot];
+    const int cur = d.cur0 ^ parity;
+    tile_two_steps<T, R, MODE, S>(d.g, phys_of(d, step), phys_of(d, step + 1).g_z, it.tz, it.tr,
+                                  (const T *)(pool + d.pop[cur][0]), (const T *)(pool + d.pop[cur][1]),
+                                  (const T *)(pool + d.aux[cur]), (T *)(pool + d.pop[cur ^ 1][0]),
+                                  (T *)(pool + d.pop[cur ^ 1][1]), (T *)(pool + d.aux[cur ^ 1]), (R *)lds);
+}
+
 struct Block {
     size_t off, size;
 };
@@ -219,7 +237,7 @@ struct lbm_axi_batch {
     std::vector<WorkItem> work;         // grouped by collision form
     std::vector<WorkItem> pair_work;    // items of the two-step launches, after `work` on the device (empty: none)
     int pair_start[NMODE + 1];
-    int pair_waves[NMODE];              // wavefronts of their workgroups, per collision form
+    TwoStepPlan plan[NMODE];            // how they go, per collision form
     int mode_start[NCLASS + 1];         // items of class q: [mode_start[q], mode_start[q + 1])
     std::vector<int> running;           // slots in the work list
     bool dirty;                         // work list / descriptors must be rebuilt
@@ -374,7 +392,7 @@ CaseDesc<R> make_desc(const lbm_axi_batch *b, const lbm_axi_case *c, const Phys<
     for (int q = 0; q < 2; ++q)
         d.aux[q] = c->aux[q] ? (uint64_t)((char *)c->aux[q] - b->pool) : 0;
     d.cur0 = c->cur ^ b->phase;
-    d.strips = pair_strips(c->prm.nz, c->prm.z_periodic, b->pair_waves[c->P64.mode]);
+    d.strips = pair_strips(c->prm.nz, c->prm.z_periodic, b->plan[c->P64.mode].waves);
     d.t0 = c->t;
     d.C = c->codec;
     return d;
@@ -441,32 +459,40 @@ bool ramping_at(const lbm_axi_case *c, int64_t t)
 }
 
 // The work lists of the two-step launches for the running cases (`order`:
-// grouped by collision form), or none.  The strips of one run of rows go to one
-// XCD (they share the lines at their edges; 64 cases of 256 x 512 in FP32:
-// 185 -> 167 us a step), run after run round the XCDs: position p runs on XCD
-// p % 8.
+// grouped by collision form), or none (FP16-deviation storage: encoding and
+// decoding bound it, not the traffic).  Marching, the strips of one run of rows
+// go to one XCD (they share the lines at their edges; 64 cases of 256 x 512 in
+// FP32: 185 -> 167 us a step), run after run round the XCDs; tiles go as eight
+// runs of neighbours.  Position p runs on XCD p % 8.
 void build_pairs(lbm_axi_batch *b, const std::vector<int> &order)
 {
     b->pair_work.clear();
     for (int q = 0; q <= NMODE; ++q) b->pair_start[q] = 0;
-    int64_t nodes = 0;
-    for (int s : order) nodes += (int64_t)b->cases[s]->prm.nr * b->cases[s]->prm.nz;
-    if (!pair_pays(nodes, b->precision)) return;
+    if (b->precision == LBM_AXI_FP16D) return;
     for (size_t first = 0, end; first < order.size(); first = end) {
         const int mode = b->cases[order[first]]->P64.mode;
         std::vector<const lbm_axi_case *> form;
         for (end = first; end < order.size() && b->cases[order[end]]->P64.mode == mode; ++end)
             form.push_back(b->cases[order[end]]);
-        const PairShape shape = pair_shape(form.data(), (int)form.size());
-        b->pair_waves[mode] = shape.waves;
+        const TwoStepPlan plan = two_step_plan(form.data(), (int)form.size());
+        b->plan[mode] = plan;
         std::vector<WorkItem> queue[8];
         int next = 0;
         for (size_t i = 0; i < form.size(); ++i) {
             const lbm_axi_params &p = form[i]->prm;
-            const int strips = pair_strips(p.nz, p.z_periodic, shape.waves);
-            for (int ra = 0; ra < p.nr; ra += shape.rows, next = (next + 1) % 8)
+            const int slot = order[first + i];
+            if (!plan.march) {
+                with_tile_shape(plan.tile, [&](auto shape) {
+                    using S = decltype(shape);
+                    const int tz = (p.nz + S::OZ - 1) / S::OZ, tr = (p.nr + S::OR - 1) / S::OR;
+                    case_items(slot, tz * tr, tz, 8, true, &b->pair_work);
+                });
+                continue;
+            }
+            const int strips = pair_strips(p.nz, p.z_periodic, plan.waves);
+            for (int ra = 0; ra < p.nr; ra += plan.rows, next = (next + 1) % 8)
                 for (int k = 0; k < strips; ++k)
-                    queue[next].push_back(WorkItem{order[first + i], k, ra, std::min(shape.rows, p.nr - ra)});
+                    queue[next].push_back(WorkItem{slot, k, ra, std::min(plan.rows, p.nr - ra)});
         }
         size_t longest = 0;
         for (const auto &x : queue) longest = std::max(longest, x.size());
@@ -601,9 +627,19 @@ template <typename T, typename R, int MODE>
 void launch_pair_part(lbm_axi_batch *b, int parity, int step)
 {
     const int first = b->pair_start[MODE], n = b->pair_start[MODE + 1] - first;
-    if (n > 0)
-        batch_pair_kernel<T, R, MODE><<<n, 64 * b->pair_waves[MODE], pair_lds_bytes<R, MODE>(b->pair_waves[MODE]), b->stream>>>(
-            b->pool, (const CaseDesc<R> *)b->d_descs, b->d_work + b->work.size() + first, parity, step);
+    if (n <= 0) return;
+    const TwoStepPlan &w = b->plan[MODE];
+    const CaseDesc<R> *descs = (const CaseDesc<R> *)b->d_descs;
+    const WorkItem *work = b->d_work + b->work.size() + first;
+    if (w.march)
+        batch_pair_kernel<T, R, MODE><<<n, 64 * w.waves, pair_lds_bytes<R, MODE>(w.waves), b->stream>>>(b->pool, descs, work,
+                                                                                                     parity, step);
+    else
+        with_tile_shape(w.tile, [&](auto shape) {
+            using S = decltype(shape);
+            batch_tile_kernel<T, R, MODE, S><<<n, S::THREADS, S::LDS_VALUES * sizeof(R), b->stream>>>(b->pool, descs, work,
+                                                                                                   parity, step);
+        });
 }
 
 template <typename T, typename R>
@@ -797,7 +833,7 @@ int lbm_axi_batch_create(void *dev_pool, size_t pool_bytes, int32_t max_cases, i
     b->dirty = true;
     for (int q = 0; q <= NCLASS; ++q) b->mode_start[q] = 0;
     for (int q = 0; q <= NMODE; ++q) b->pair_start[q] = 0;
-    for (int &w : b->pair_waves) w = 1;
+    for (TwoStepPlan &w : b->plan) w = TwoStepPlan{false, 1, 4, 0};
     b->launches = 0;
     *out = b;
     return LBM_AXI_OK;

@@ -1,13 +1,12 @@
-"""Two time steps per launch (large FP64 and FP32 cases and batches) against
-one step per launch: the same operations on every node, so the same bits."""
+"""Two time steps per launch (FP64 and FP32 cases and batches, marching strips
+or in tiles, by size) against one step per launch: the same operations on every
+node, so the same bits."""
 import numpy as np
 import pytest
 
 from paper_1810_09299_amd import inputs
 
 pytestmark = pytest.mark.gpu
-
-PAIRED_NODES = 700_000      # nodes of a case or batch from which steps run in pairs
 
 
 def _spec(nr, nz, zper, collision):
@@ -40,16 +39,19 @@ GRIDS = [(4, 4), (5, 7), (9, 54), (16, 55), (7, 64), (12, 65), (20, 118), (33, 1
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
 @pytest.mark.parametrize("collision", ["mrt", "general", "srt", "nmrt"])
-def test_batch_pairs_equal_single_steps(precision, collision):
-    """Small and odd grids, periodic and walled, beside a large one that makes
-    the batch run two steps per launch; 7 steps: three pairs and an odd step."""
+@pytest.mark.parametrize("beside", [None, (101, 331), (301, 501), (1201, 1001)])
+def test_batch_pairs_equal_single_steps(precision, collision, beside):
+    """Small and odd grids, periodic and walled; the case beside them decides
+    how the batch goes: the three smallest alone (8 x 4 tiles), in larger tiles,
+    or marching.  7 steps: three pairs and an odd step."""
     from paper_1810_09299_amd.batch import Batch
-    specs = [_spec(nr, nz, zper, collision) for nr, nz in GRIDS for zper in (True, False)]
-    big = _spec(701, 1001, True, collision)
-    assert big.nodes > PAIRED_NODES
-    b = Batch(pool_bytes=Batch.pool_for(specs + [big], precision), max_cases=len(specs) + 1, precision=precision)
+    specs = [_spec(nr, nz, zper, collision) for nr, nz in (GRIDS if beside else GRIDS[:3]) for zper in (True, False)]
+    more = [_spec(*beside, True, collision)] if beside else []
+    b = Batch(pool_bytes=Batch.pool_for(specs + more, precision), max_cases=len(specs) + len(more),
+              precision=precision)
     slots = [b.admit(s, 7) for s in specs]
-    b.admit(big, 8)
+    for s in more:
+        b.admit(s, 8)
     b.run(7)
     for s, slot in zip(specs, slots):
         f, g, aux, t = b.get_state(slot)
@@ -60,16 +62,20 @@ def test_batch_pairs_equal_single_steps(precision, collision):
     b.close()
 
 
-@pytest.mark.parametrize("precision,nr,nz,zper", [("fp64", 353, 2003, True), ("fp64", 1405, 500, False),
-                                                  ("fp32", 353, 2003, False), ("fp32", 1370, 512, True),
-                                                  ("fp32", 5600, 128, False)])
+# in tiles of each shape (from 8 x 4 up; 32 x 16, and in FP64 beyond 256 of them
+# 16 x 16), and marching
+CASES = [("fp32", 64, 128, False), ("fp64", 33, 65, True), ("fp64", 61, 286, True), ("fp32", 149, 301, False),
+         ("fp32", 255, 509, True), ("fp64", 250, 511, False), ("fp64", 131, 2040, True), ("fp64", 405, 2003, True),
+         ("fp64", 1605, 500, False), ("fp32", 601, 2003, False), ("fp32", 2370, 512, True), ("fp32", 9600, 128, False)]
+
+
+@pytest.mark.parametrize("precision,nr,nz,zper", CASES)
 def test_case_pairs_equal_single_steps(precision, nr, nz, zper):
-    """One large case: any split of the steps into calls gives the same state,
-    and reading it back (whose fields use the other population buffer) or
-    loading a state between pairs leaves the next steps right."""
+    """One case: any split of the steps into calls gives the same state, and
+    reading it back (whose fields use the other population buffer) or loading a
+    state between pairs leaves the next steps right."""
     from paper_1810_09299_amd.case import AxiCase
     spec = _spec(nr, nz, zper, "mrt")
-    assert spec.nodes >= PAIRED_NODES
     ref = _single_steps(spec, precision, 8)
     c = AxiCase(spec, precision=precision)
     c.step(5)
@@ -88,12 +94,13 @@ def test_case_pairs_equal_single_steps(precision, nr, nz, zper):
     c.close()
 
 
-def test_recorded_steps_replay_from_their_own_result():
+@pytest.mark.parametrize("nr,nz", [(64, 128), (601, 2003)])
+def test_recorded_steps_replay_from_their_own_result(nr, nz):
     """Steps recorded into a graph go one by one: an even number of them ends in
     the buffer they started from, so replays continue each other."""
     import torch
     from paper_1810_09299_amd.case import AxiCase
-    spec = _spec(701, 1001, True, "mrt")
+    spec = _spec(nr, nz, True, "mrt")
     spec.g_ramp = 0.0                                 # a recording holds the acceleration of its own steps
     ref = _single_steps(spec, "fp32", 6)
     stream = torch.cuda.Stream()
