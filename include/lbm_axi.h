@@ -207,8 +207,9 @@ int lbm_axi_set_state(lbm_axi_case *c, const double *f, const double *g, const d
 /* Current time step of the case. */
 int lbm_axi_time(const lbm_axi_case *c, int64_t *t);
 
-/* Selects the step kernel's tile (tile_r rows by 64 columns; tile_r in
- * {2, 4, 8, 16}); the results do not depend on it.  0 picks the default. */
+/* Selects the tile of the kernel that advances one step per launch (tile_r rows
+ * by 64 columns; tile_r in {2, 4, 8, 16}); the results do not depend on it.  0
+ * picks the default, by precision and size. */
 int lbm_axi_set_tile(lbm_axi_case *c, int32_t tile_r);
 
 /* Frees the handle (not the caller's device block).  NULL is accepted. */

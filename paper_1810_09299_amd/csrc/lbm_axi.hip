@@ -1133,6 +1133,19 @@ TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n)
     return plan;
 }
 
+// Rows of the single step's tile where the caller names none: 8, or, in
+// FP16-deviation storage, 4 while every such tile has a compute unit to itself
+// (then it is the time of one tile that counts: 150 x 300 5.6 us a step against
+// 6.1, 128 x 256 5.4 against 5.7; beyond, the larger share of ring costs more:
+// 256 x 512 6.3 against 6.0).  FP64 and FP32 step singly only for an odd step
+// out or in a recording: 64 x 128 FP32 measured the same either way.
+static int default_tile(const lbm_axi_case *c)
+{
+    if (c->prm.precision != LBM_AXI_FP16D) return 8;
+    const int64_t tiles = (int64_t)((c->prm.nz + TZ - 1) / TZ) * ((c->prm.nr + 3) / 4);
+    return tiles <= c->cus ? 4 : 8;
+}
+
 HalfBuf half_buf(const lbm_axi_case *c, int b)
 {
     const int64_t pl = c->geom.plane;
@@ -1222,7 +1235,9 @@ int lbm_axi_init(const lbm_axi_params *params, void *dev_state, size_t dev_bytes
     c->bytes = dev_bytes;
     c->t = 0;
     c->cur = 0;
-    c->tile_r = 8;
+    c->cus = 256;
+    (void)hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev);
+    c->tile_r = default_tile(c);
     c->esize = L.esize;
     for (int b = 0; b < 2; ++b)
         for (int q = 0; q < 2; ++q)
@@ -1236,8 +1251,6 @@ int lbm_axi_init(const lbm_axi_params *params, void *dev_state, size_t dev_bytes
     c->P32 = make_phys<float>(params);
     c->codec = make_codec(params);
     c->geom = geom_for(c, c->tile_r);
-    c->cus = 256;
-    (void)hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev);
     c->two = two_step_plan(&c, 1);
 
     int64_t nn = (int64_t)params->nr * params->nz;
@@ -1396,7 +1409,7 @@ int lbm_axi_time(const lbm_axi_case *c, int64_t *t)
 int lbm_axi_set_tile(lbm_axi_case *c, int32_t tile_r)
 {
     if (!c) return LBM_AXI_ESTATE;
-    if (tile_r == 0) tile_r = 8;
+    if (tile_r == 0) tile_r = default_tile(c);
     if (tile_r != 2 && tile_r != 4 && tile_r != 8 && tile_r != 16) return LBM_AXI_EINVAL;
     c->tile_r = tile_r;
     c->geom = geom_for(c, tile_r);

@@ -148,3 +148,27 @@ def test_phase_mass_conserved_exactly(name, steps):
     _, d1, rc1 = c.moments(fields=False)
     assert rc0 == 0 and rc1 == 0
     assert abs(d1["phase_mass"] - d0["phase_mass"]) <= 1e-14 * d0["phase_mass"]
+
+
+@pytest.mark.parametrize("nr,nz", [(1024, 64), (1025, 64), (5, 65)])
+def test_fp16_default_tile(nr, nz):
+    """The default tile height goes by the number of 64 x 4 tiles (256 of them
+    and one row of them more): the same bits as every named height."""
+    from paper_1810_09299_amd.case import AxiCase
+    spec = inputs.static_droplet(nr=nr, nz=nz, R=max(2.0, 0.3 * min(nr, nz)), W=4.0, ratio=10.0, sigma=1e-3)
+    state = inputs.random_state(nr, nz, seed=3)
+
+    def after(tile):
+        c = AxiCase(spec, precision="fp16")
+        c.set_state(*state, 0)
+        if tile is not None:
+            c.set_tile(tile)
+        c.step(3)
+        s = c.get_state()
+        c.close()
+        return s
+
+    default = after(None)
+    for tile in (0, 4, 8):
+        for a, b in zip(default, after(tile)):
+            assert np.array_equal(a, b)
