@@ -159,7 +159,9 @@ def _check(rc: int, where: str, ok=(LBM_AXI_OK,)) -> int:
 def _dptr(a):
     if a is None:
         return None
-    return a.ctypes.data_as(_D)
+    # the address alone: data_as would tie the array into a reference cycle, and
+    # every result would stay allocated until the collector's next run
+    return ctypes.cast(a.ctypes.data, _D)
 
 
 # ---------------------------------------------------------------- same names

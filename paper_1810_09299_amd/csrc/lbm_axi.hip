@@ -1202,6 +1202,88 @@ __global__ __launch_bounds__(256) void device_copy_kernel(const copy_vec *__rest
 }
 } // namespace
 
+// The planes of a state through the transfer plane, in stream order: the caller
+// waits once, for all of them (and on an error for what was enqueued before it).
+static int enqueue_get(lbm_axi_case *c, double *f, double *g, double *aux)
+{
+    Geom G = c->geom;
+    int64_t nn = (int64_t)G.nr * G.nz;
+    unsigned nb = blocks_for(nn, 256);
+    const bool half = c->prm.precision == LBM_AXI_FP16D;
+    double *outs[2] = {f, g};
+    for (int q = 0; q < 2; ++q) {
+        if (!outs[q]) continue;
+        for (int i = 0; i < 9; ++i) {
+            if (half)
+                gather_plane_h<<<nb, 256, 0, c->stream>>>(G, c->codec, half_buf(c, c->cur), i, q, c->xfer);
+            else if (c->prm.precision == LBM_AXI_FP64)
+                gather_plane_kernel<double><<<nb, 256, 0, c->stream>>>(G, i, (const double *)c->pop[c->cur][q], c->xfer);
+            else
+                gather_plane_kernel<float><<<nb, 256, 0, c->stream>>>(G, i, (const float *)c->pop[c->cur][q], c->xfer);
+            if (launch_ok()) return LBM_AXI_EDEVICE;
+            HIP_OK(hipMemcpyAsync(outs[q] + i * nn, c->xfer, nn * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+        }
+    }
+    if (aux) {
+        for (int q = 0; q < 3; ++q) {
+            if (half)
+                convert_kernel<float, double><<<nb, 256, 0, c->stream>>>(
+                    nn, q == 0 ? half_buf(c, c->cur).phi : (const float *)c->aux[0] + q * G.plane, c->xfer);
+            else if (c->prm.precision == LBM_AXI_FP64)
+                convert_kernel<double, double><<<nb, 256, 0, c->stream>>>(nn, (const double *)c->aux[c->cur] + q * G.plane, c->xfer);
+            else
+                convert_kernel<float, double><<<nb, 256, 0, c->stream>>>(nn, (const float *)c->aux[c->cur] + q * G.plane, c->xfer);
+            if (launch_ok()) return LBM_AXI_EDEVICE;
+            HIP_OK(hipMemcpyAsync(aux + q * nn, c->xfer, nn * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+        }
+    }
+    return LBM_AXI_OK;
+}
+
+static int enqueue_set(lbm_axi_case *c, const double *f, const double *g, const double *aux)
+{
+    Geom G = c->geom;
+    int64_t nn = (int64_t)G.nr * G.nz;
+    unsigned nb = blocks_for(nn, 256);
+    const bool half = c->prm.precision == LBM_AXI_FP16D;
+    if (half) {
+        // the stored phase field first: FP16 f values are encoded against it
+        for (int q = 0; q < 3; ++q) {
+            HIP_OK(hipMemcpyAsync(c->xfer, aux + q * nn, nn * sizeof(double), hipMemcpyHostToDevice, c->stream));
+            convert_kernel<double, float><<<nb, 256, 0, c->stream>>>(
+                nn, c->xfer, q == 0 ? half_buf(c, c->cur).phi : (float *)c->aux[0] + q * G.plane);
+            if (launch_ok()) return LBM_AXI_EDEVICE;
+        }
+    }
+    const double *ins[2] = {f, g};
+    for (int q = 0; q < 2; ++q)
+        for (int i = 0; i < 9; ++i) {
+            HIP_OK(hipMemcpyAsync(c->xfer, ins[q] + i * nn, nn * sizeof(double), hipMemcpyHostToDevice, c->stream));
+            if (half)
+                scatter_plane_h<<<nb, 256, 0, c->stream>>>(G, c->codec, half_buf(c, c->cur), i, q, c->xfer);
+            else if (c->prm.precision == LBM_AXI_FP64)
+                scatter_plane_kernel<double><<<nb, 256, 0, c->stream>>>(G, i, c->xfer, (double *)c->pop[c->cur][q]);
+            else
+                scatter_plane_kernel<float><<<nb, 256, 0, c->stream>>>(G, i, c->xfer, (float *)c->pop[c->cur][q]);
+            if (launch_ok()) return LBM_AXI_EDEVICE;
+        }
+    for (int q = 0; q < 3 && !half; ++q) {
+        HIP_OK(hipMemcpyAsync(c->xfer, aux + q * nn, nn * sizeof(double), hipMemcpyHostToDevice, c->stream));
+        if (c->prm.precision == LBM_AXI_FP64)
+            convert_kernel<double, double><<<nb, 256, 0, c->stream>>>(nn, c->xfer, (double *)c->aux[c->cur] + q * G.plane);
+        else
+            convert_kernel<double, float><<<nb, 256, 0, c->stream>>>(nn, c->xfer, (float *)c->aux[c->cur] + q * G.plane);
+        if (launch_ok()) return LBM_AXI_EDEVICE;
+    }
+    return LBM_AXI_OK;
+}
+
+static int finish(lbm_axi_case *c, int rc)
+{
+    const hipError_t e = hipStreamSynchronize(c->stream);
+    return rc ? rc : (e == hipSuccess ? LBM_AXI_OK : LBM_AXI_EDEVICE);
+}
+
 extern "C" {
 
 size_t lbm_axi_state_bytes(const lbm_axi_params *params)
@@ -1318,39 +1400,8 @@ int lbm_axi_moments_noalloc(lbm_axi_case *c, double *phi, double *rho, double *u
 int lbm_axi_get_state(lbm_axi_case *c, double *f, double *g, double *aux, int64_t *t)
 {
     if (!c) return LBM_AXI_ESTATE;
-    Geom G = c->geom;
-    int64_t nn = (int64_t)G.nr * G.nz;
-    unsigned nb = blocks_for(nn, 256);
-    const bool half = c->prm.precision == LBM_AXI_FP16D;
-    double *outs[2] = {f, g};
-    for (int q = 0; q < 2; ++q) {
-        if (!outs[q]) continue;
-        for (int i = 0; i < 9; ++i) {
-            if (half)
-                gather_plane_h<<<nb, 256, 0, c->stream>>>(G, c->codec, half_buf(c, c->cur), i, q, c->xfer);
-            else if (c->prm.precision == LBM_AXI_FP64)
-                gather_plane_kernel<double><<<nb, 256, 0, c->stream>>>(G, i, (const double *)c->pop[c->cur][q], c->xfer);
-            else
-                gather_plane_kernel<float><<<nb, 256, 0, c->stream>>>(G, i, (const float *)c->pop[c->cur][q], c->xfer);
-            if (launch_ok()) return LBM_AXI_EDEVICE;
-            HIP_OK(hipMemcpyAsync(outs[q] + i * nn, c->xfer, nn * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-            HIP_OK(hipStreamSynchronize(c->stream));
-        }
-    }
-    if (aux) {
-        for (int q = 0; q < 3; ++q) {
-            if (half)
-                convert_kernel<float, double><<<nb, 256, 0, c->stream>>>(
-                    nn, q == 0 ? half_buf(c, c->cur).phi : (const float *)c->aux[0] + q * G.plane, c->xfer);
-            else if (c->prm.precision == LBM_AXI_FP64)
-                convert_kernel<double, double><<<nb, 256, 0, c->stream>>>(nn, (const double *)c->aux[c->cur] + q * G.plane, c->xfer);
-            else
-                convert_kernel<float, double><<<nb, 256, 0, c->stream>>>(nn, (const float *)c->aux[c->cur] + q * G.plane, c->xfer);
-            if (launch_ok()) return LBM_AXI_EDEVICE;
-            HIP_OK(hipMemcpyAsync(aux + q * nn, c->xfer, nn * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-            HIP_OK(hipStreamSynchronize(c->stream));
-        }
-    }
+    const int rc = finish(c, enqueue_get(c, f, g, aux));
+    if (rc) return rc;
     if (t) *t = c->t;
     return LBM_AXI_OK;
 }
@@ -1359,42 +1410,8 @@ int lbm_axi_set_state(lbm_axi_case *c, const double *f, const double *g, const d
 {
     if (!c) return LBM_AXI_ESTATE;
     if (!f || !g || !aux || t < 0) return LBM_AXI_EINVAL;
-    Geom G = c->geom;
-    int64_t nn = (int64_t)G.nr * G.nz;
-    unsigned nb = blocks_for(nn, 256);
-    const bool half = c->prm.precision == LBM_AXI_FP16D;
-    if (half) {
-        // the stored phase field first: FP16 f values are encoded against it
-        for (int q = 0; q < 3; ++q) {
-            HIP_OK(hipMemcpyAsync(c->xfer, aux + q * nn, nn * sizeof(double), hipMemcpyHostToDevice, c->stream));
-            convert_kernel<double, float><<<nb, 256, 0, c->stream>>>(
-                nn, c->xfer, q == 0 ? half_buf(c, c->cur).phi : (float *)c->aux[0] + q * G.plane);
-            if (launch_ok()) return LBM_AXI_EDEVICE;
-            HIP_OK(hipStreamSynchronize(c->stream));
-        }
-    }
-    const double *ins[2] = {f, g};
-    for (int q = 0; q < 2; ++q)
-        for (int i = 0; i < 9; ++i) {
-            HIP_OK(hipMemcpyAsync(c->xfer, ins[q] + i * nn, nn * sizeof(double), hipMemcpyHostToDevice, c->stream));
-            if (half)
-                scatter_plane_h<<<nb, 256, 0, c->stream>>>(G, c->codec, half_buf(c, c->cur), i, q, c->xfer);
-            else if (c->prm.precision == LBM_AXI_FP64)
-                scatter_plane_kernel<double><<<nb, 256, 0, c->stream>>>(G, i, c->xfer, (double *)c->pop[c->cur][q]);
-            else
-                scatter_plane_kernel<float><<<nb, 256, 0, c->stream>>>(G, i, c->xfer, (float *)c->pop[c->cur][q]);
-            if (launch_ok()) return LBM_AXI_EDEVICE;
-            HIP_OK(hipStreamSynchronize(c->stream));
-        }
-    for (int q = 0; q < 3 && !half; ++q) {
-        HIP_OK(hipMemcpyAsync(c->xfer, aux + q * nn, nn * sizeof(double), hipMemcpyHostToDevice, c->stream));
-        if (c->prm.precision == LBM_AXI_FP64)
-            convert_kernel<double, double><<<nb, 256, 0, c->stream>>>(nn, c->xfer, (double *)c->aux[c->cur] + q * G.plane);
-        else
-            convert_kernel<double, float><<<nb, 256, 0, c->stream>>>(nn, c->xfer, (float *)c->aux[c->cur] + q * G.plane);
-        if (launch_ok()) return LBM_AXI_EDEVICE;
-        HIP_OK(hipStreamSynchronize(c->stream));
-    }
+    const int rc = finish(c, enqueue_set(c, f, g, aux));
+    if (rc) return rc;
     c->t = t;
     return LBM_AXI_OK;
 }
