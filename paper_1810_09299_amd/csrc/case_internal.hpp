@@ -23,7 +23,7 @@ constexpr int PLANE_PAD = AXI_PLANE_PAD;   // spare elements per population plan
 struct TwoStepPlan {
     bool march;            // strips marching up the rows (axi_pair.hpp), else tiles (axi_tile.hpp)
     int waves, rows;       // march: wavefronts of a workgroup, rows of a run
-    int tile;              // tiles: the shape (with_tile_shape)
+    int tile;              // tiles: the shape (with_tile_shape); -1: steps go singly
 };
 
 } // namespace axi
@@ -60,7 +60,8 @@ int64_t plane_elems(int nr, int nz);
 // how many strips `waves` wavefronts cut nz columns into (axi_pair.hpp)
 int pair_strips(int nz, int z_periodic, int waves);
 // two steps per launch for the n cases of one launch: the plan that suits them
-TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n);
+// (singly: one case, which may also step singly)
+TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool singly);
 // FP16-deviation storage: buffers of ping-pong side b, and the step from side cur
 struct HalfBuf {
     float *f0;       // f_0 plane (FP32)

@@ -12,7 +12,10 @@
 // plane = nr*nz rounded up to 64 elements, plus 64; SoA, z fastest.
 //   diag                 the diagnostics record (lbm_axi_diag) reduced on the device
 //
-// One step = one launch of step_kernel: every workgroup owns a 64 x TR tile,
+// Two steps of an FP64 or FP32 case are one launch of pair_kernel (large cases,
+// axi_pair.hpp) or tile_kernel (small ones, axi_tile.hpp).  A step on its own --
+// the odd one out, in a recording, FP16-deviation storage -- is one
+// launch of step_kernel: every workgroup owns a 64 x TR tile,
 // pulls the f populations of its tile plus a 2-cell ring (the ring's extra
 // reads hit L2), forms phi in LDS, and then finishes its own nodes: stencil,
 // pressure, velocity, both collisions, store.  No grid-wide synchronisation.
@@ -968,7 +971,7 @@ bool recording(hipStream_t stream)
 
 int do_steps(lbm_axi_case *c, int64_t n)
 {
-    if (n >= 2 && c->prm.precision != LBM_AXI_FP16D && !recording(c->stream)) {
+    if (n >= 2 && c->prm.precision != LBM_AXI_FP16D && c->two.tile >= 0 && !recording(c->stream)) {
         for (; n >= 2; n -= 2) {
             if (c->prm.precision == LBM_AXI_FP64)
                 launch_two<double, double>(c, c->P64);
@@ -1099,15 +1102,27 @@ static void plan_march(const lbm_axi_case *const *cases, int n, TwoStepPlan &bes
 // 512 x 1024 21.5 us a step against 15.2 in tiles, of 512 x 2048 30 against 28,
 // 16 cases of 256 x 512 46 against 57; FP64, 512 x 1024 30 against 26, 512 x
 // 2048 51 against 59.
-// Tiles: the smallest that still gives every compute unit at most one, since
-// smaller ones are sooner done (64 x 128 FP32: 3.4 us a step in 8 x 4, 3.5 in
-// 12 x 8, 4.1 in 16 x 16; 60 x 286 FP64: 4.3 in 12 x 8, 5.5 in 16 x 16; 128 x
-// 512 FP32: 4.4 in 16 x 16, 5.8 in 32 x 16); beyond that the one with the
-// smaller share of halo, in FP64 the one of which two fit a compute unit's LDS
-// (128 x 2048: 15.8 in 16 x 16, 17.1 in 32 x 16; FP32 10.6 and 9.4).
+// Tiles: the shape whose launch is done first.  A compute unit takes its tiles
+// together or in turn; either way a step takes what a launch and the first
+// latencies do and a share per tile of the fullest unit (TileCost; fitted, within
+// 10 %, to grids of 2 to 690 thousand nodes: 64 x 128 FP32 3.4 us a step in
+// 8 x 4, 3.5 in 12 x 8, 4.1 in 16 x 16; 128 x 512 FP32 4.5 in 16 x 16, 5.4 in
+// 12 x 8, 5.9 in 32 x 16; 300 x 600 FP32 9.7 in 12 x 8, 8.1 in 16 x 16, 8.4 in 32 x 16;
+// 128 x 2048 10.5 and 9.3 in the last two, FP64 15.9 and 16.9).
 // Single steps took 5.2 (64 x 128, FP32, the default tile), 7.8 (60 x 286,
-// FP64), 11.1 (128 x 2048, FP32).
-TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n)
+// FP64), 11.1 (128 x 2048, FP32).  Only where they, in 64 x 8, need one tile per
+// unit and the smaller tiles of two steps, by their ragged edges, more, do they
+// stay ahead in FP32 (69 x 1717: 7.7 against 8.5), so a case steps singly there.
+struct TileCost {
+    float launch, tile;      // us a step
+};
+constexpr TileCost TILE_COST[2][TILE_SHAPES] = {
+    {{2.5f, 0.85f}, {2.85f, 0.83f}, {2.7f, 1.75f}, {2.9f, 3.0f}},   // FP32
+    {{2.6f, 1.27f}, {3.0f, 1.4f}, {2.85f, 2.8f}, {0.9f, 7.2f}},     // FP64
+};
+constexpr float SINGLE_COST = 7.7f;
+
+TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool singly)
 {
     TwoStepPlan plan{false, 1, 4, 0};
     const bool fp64 = cases[0]->prm.precision == LBM_AXI_FP64;
@@ -1118,18 +1133,23 @@ TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n)
         plan_march(cases, n, plan);
         return plan;
     }
-    auto groups = [&](int shape) {
-        int64_t s = 0;
+    const int64_t cus = cases[0]->cus;
+    float best = 0.0f;
+    for (int shape = 0; shape < TILE_SHAPES; ++shape) {
+        int64_t tiles = 0;
         with_tile_shape(shape, [&](auto t) {
             using S = decltype(t);
             for (int i = 0; i < n; ++i)
-                s += (int64_t)((cases[i]->prm.nz + S::OZ - 1) / S::OZ) * ((cases[i]->prm.nr + S::OR - 1) / S::OR);
+                tiles += (int64_t)((cases[i]->prm.nz + S::OZ - 1) / S::OZ) * ((cases[i]->prm.nr + S::OR - 1) / S::OR);
         });
-        return s;
-    };
-    for (plan.tile = 0; plan.tile < TILE_SHAPES; ++plan.tile)
-        if (groups(plan.tile) <= cases[0]->cus) return plan;
-    plan.tile = fp64 ? 2 : 3;
+        const TileCost c = TILE_COST[fp64 ? 1 : 0][shape];
+        const float cost = c.launch + c.tile * (float)((tiles + cus - 1) / cus);
+        if (shape == 0 || cost <= best) {
+            best = cost;
+            plan.tile = shape;
+        }
+    }
+    if (singly && !fp64 && best > SINGLE_COST && geom_for(cases[0], 8).tiles <= cus) plan.tile = -1;
     return plan;
 }
 
@@ -1333,7 +1353,7 @@ int lbm_axi_init(const lbm_axi_params *params, void *dev_state, size_t dev_bytes
     c->P32 = make_phys<float>(params);
     c->codec = make_codec(params);
     c->geom = geom_for(c, c->tile_r);
-    c->two = two_step_plan(&c, 1);
+    c->two = two_step_plan(&c, 1, true);
 
     int64_t nn = (int64_t)params->nr * params->nz;
     if (hipMemcpyAsync(c->xfer, phi0_host, nn * sizeof(double), hipMemcpyHostToDevice, c->stream) != hipSuccess) {

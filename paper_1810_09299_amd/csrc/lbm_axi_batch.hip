@@ -1,16 +1,18 @@
 // lbm_axi batches: many independent cases of different sizes and step counts
-// advanced together, one fused launch per time step for all of them.
+// advanced together, in fused launches that take all of them on.
 //
 // Memory: the caller hands over one device pool.  Its head holds the case
 // table (CaseDesc per slot) and the work list; the rest is carved first-fit
 // into per-case blocks (the same layout as a single case), so admission is
 // decided by HBM footprint.
 //
-// A step of the batch is one launch of batch_step_kernel over the work list
-// (one per collision form present, see COLLIDE_*):
-// item w = (slot, tile) runs the same tile body as the single-case kernel, so
-// every case's populations are bit-identical to running it alone.  Runs of
-// steps with an unchanged set of running cases replay a captured hipGraph.
+// FP64 and FP32 batches advance two steps per launch where both are wanted
+// (build_pairs: marching strips or tiles, by size); the odd step out, and every
+// step in FP16-deviation storage, is a launch of batch_step_kernel(_h) over the
+// work list (one per collision form present, see COLLIDE_*): item w = (slot,
+// tile) runs the same tile body as the single-case kernel.  Either way every
+// case's populations are bit-identical to running it alone.  Runs of steps with
+// an unchanged set of running cases replay a captured hipGraph.
 // The host keeps each case's step count and ping-pong parity; a case stops
 // exactly at its requested number of steps.
 //
@@ -459,8 +461,9 @@ bool ramping_at(const lbm_axi_case *c, int64_t t)
 }
 
 // The work lists of the two-step launches for the running cases (`order`:
-// grouped by collision form), or none (FP16-deviation storage: encoding and
-// decoding bound it, not the traffic).  Marching, the strips of one run of rows
+// grouped by collision form), or none (FP16-deviation storage: a second step in
+// the launch pays its encoding and decoding again, on the halo too; in tiles
+// 150 x 300 took 6.4 us a step against 5.6 singly, 256 x 512 8.9 against 5.9).  Marching, the strips of one run of rows
 // go to one XCD (they share the lines at their edges; 64 cases of 256 x 512 in
 // FP32: 185 -> 167 us a step), run after run round the XCDs; tiles go as eight
 // runs of neighbours.  Position p runs on XCD p % 8.
@@ -474,7 +477,7 @@ void build_pairs(lbm_axi_batch *b, const std::vector<int> &order)
         std::vector<const lbm_axi_case *> form;
         for (end = first; end < order.size() && b->cases[order[end]]->P64.mode == mode; ++end)
             form.push_back(b->cases[order[end]]);
-        const TwoStepPlan plan = two_step_plan(form.data(), (int)form.size());
+        const TwoStepPlan plan = two_step_plan(form.data(), (int)form.size(), false);
         b->plan[mode] = plan;
         std::vector<WorkItem> queue[8];
         int next = 0;
