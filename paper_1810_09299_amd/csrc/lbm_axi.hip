@@ -1112,7 +1112,8 @@ static void plan_march(const lbm_axi_case *const *cases, int n, TwoStepPlan &bes
 // Single steps took 5.2 (64 x 128, FP32, the default tile), 7.8 (60 x 286,
 // FP64), 11.1 (128 x 2048, FP32).  Only where they, in 64 x 8, need one tile per
 // unit and the smaller tiles of two steps, by their ragged edges, more, do they
-// stay ahead in FP32 (69 x 1717: 7.7 against 8.5), so a case steps singly there.
+// stay ahead (69 x 1717 FP32: 7.7 against 8.5; 133 x 920 FP64, SRT: 11.5 against
+// 13.2), so a case steps singly there.
 struct TileCost {
     float launch, tile;      // us a step
 };
@@ -1120,7 +1121,7 @@ constexpr TileCost TILE_COST[2][TILE_SHAPES] = {
     {{2.5f, 0.85f}, {2.85f, 0.83f}, {2.7f, 1.75f}, {2.9f, 3.0f}},   // FP32
     {{2.6f, 1.27f}, {3.0f, 1.4f}, {2.85f, 2.8f}, {0.9f, 7.2f}},     // FP64
 };
-constexpr float SINGLE_COST = 7.7f;
+constexpr float SINGLE_COST[2] = {7.7f, 11.0f};
 
 TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool singly)
 {
@@ -1149,7 +1150,7 @@ TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool singly)
             plan.tile = shape;
         }
     }
-    if (singly && !fp64 && best > SINGLE_COST && geom_for(cases[0], 8).tiles <= cus) plan.tile = -1;
+    if (singly && best > SINGLE_COST[fp64 ? 1 : 0] && geom_for(cases[0], 8).tiles <= cus) plan.tile = -1;
     return plan;
 }
 

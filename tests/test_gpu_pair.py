@@ -63,8 +63,9 @@ def test_batch_pairs_equal_single_steps(precision, collision, beside):
 
 
 # in tiles of each shape (one and several to a compute unit), singly where that
-# is ahead (69 x 1717), and marching
-CASES = [("fp32", 52, 1073, True), ("fp64", 52, 1073, False), ("fp32", 69, 1717, False), ("fp32", 300, 600, True),
+# is ahead (69 x 1717, 133 x 920), and marching
+CASES = [("fp64", 133, 920, True),
+         ("fp32", 52, 1073, True), ("fp64", 52, 1073, False), ("fp32", 69, 1717, False), ("fp32", 300, 600, True),
          ("fp32", 64, 128, False), ("fp64", 33, 65, True), ("fp64", 61, 286, True), ("fp32", 149, 301, False),
          ("fp32", 255, 509, True), ("fp64", 250, 511, False), ("fp64", 131, 2040, True), ("fp64", 405, 2003, True),
          ("fp64", 1605, 500, False), ("fp32", 601, 2003, False), ("fp32", 2370, 512, True), ("fp32", 9600, 128, False)]
