@@ -4,8 +4,9 @@
 Workload: the viscous-droplet-oscillation case, Nr x Nz = 256 x 512 (r x z),
 periodic in z, density ratio 1000, synthetic seeded initial fields; solved as a
 batch of --cases independent cases (jitter seeds 1..B; 64 cases hold 1.6 GB in
-FP32, six times the 256 MB Infinity Cache), every step one fused
-collide-and-stream launch over all of them.  The steps run as hipGraph
+FP32, six times the 256 MB Infinity Cache), advanced by fused
+collide-and-stream launches over all of them: two steps per launch in FP64 and
+FP32 storage, one in FP16-deviation storage.  The steps run as hipGraph
 replays of chunks of min(100, --steps) steps plus a directly launched tail
 (step_plan); warm-up runs --warmup steps the same way, and the graphs the
 timed runs replay are captured before the timed region.  Prints one JSON line:
@@ -13,9 +14,10 @@ timed runs replay are captured before the timed region.  Prints one JSON line:
   value         whole-job lattice updates per second, MLUPS (states resident in
                 HBM; the timed region holds exactly --steps steps of the batch)
   roofline      the batched step kernel against MI355X's 8 TB/s HBM:
-                algorithmic bytes per launch (cases x nodes x bytes per lattice
-                update) over the mean launch duration, from HIP events on the
-                batch's stream around the timed region
+                algorithmic bytes per launch (the state of every node read once
+                and written once) over the mean launch duration, from HIP events
+                on the batch's stream around the timed region;
+                steps_per_launch steps each
   variants      the batch in the other storage precisions; the batch with the
                 SRT and non-orthogonal MRT collision forms in every precision;
                 FP16-deviation storage with stochastic g rounding; single case
@@ -47,12 +49,14 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-# algorithmic HBM bytes per lattice update, read + write: 18 populations and 3
+# algorithmic HBM bytes per node and launch, read + write: 18 populations and 3
 # aux values (phi, u_z, u_r) of the storage type; FP16-deviation storage: 18
 # FP16 populations and FP32 aux.  (Its implementation keeps f_0 in FP32 for
 # exact mass and so moves 100 B; the algorithmic count is the method's 96 B.)
 BYTES_PER_LU = {"fp64": 18 * 8 * 2 + 3 * 8 * 2, "fp32": 18 * 4 * 2 + 3 * 4 * 2,
                 "fp16": 18 * 2 * 2 + 3 * 4 * 2}
+# time steps that one launch advances
+STEPS_PER_LAUNCH = {"fp64": 2, "fp32": 2, "fp16": 1}
 MOVED_BYTES_PER_LU = dict(BYTES_PER_LU, fp16=(4 + 8 * 2 + 9 * 2) * 2 + 3 * 4 * 2)
 WORKLOAD = "oscillating_droplet"
 CHUNK = 100
@@ -70,6 +74,7 @@ def kernel_source_hash() -> str:
     h = hashlib.sha256()
     for rel in ("paper_1810_09299_amd/csrc/lbm_axi.hip", "paper_1810_09299_amd/csrc/lbm_axi_batch.hip",
                 "paper_1810_09299_amd/csrc/axi_device.hpp", "paper_1810_09299_amd/csrc/axi_half.hpp",
+                "paper_1810_09299_amd/csrc/axi_pair.hpp", "paper_1810_09299_amd/csrc/axi_tile.hpp",
                 "paper_1810_09299_amd/csrc/case_internal.hpp", "paper_1810_09299_amd/build.py"):
         with open(os.path.join(ROOT, rel), "rb") as fh:
             h.update(fh.read())
@@ -91,13 +96,16 @@ def step_plan(steps: int, chunk: int = CHUNK) -> list:
 def measured_traffic(precision: str, config, cases: int) -> float | None:
     """HBM bytes per launch from the committed rocprofv3 counter summary, if it
     was taken on the current kernel source with the same number of cases and
-    launch configuration (tile rows, persistent, schedule, bands); else None."""
+    launch configuration (tile rows, persistent, schedule, bands; a launch of
+    two steps takes none of these); else None."""
     path = os.path.join(ROOT, "profiles", "batch_step_kernel_oscillating_droplet_traffic.json")
     if not os.path.exists(path):
         return None
     with open(path) as fh:
         d = json.load(fh)
     key = f"{cases}/{config['tile_rows']}/{config['persistent']}/{config['schedule']}/{config['bands']}"
+    if STEPS_PER_LAUNCH[precision] == 2:
+        key = f"{cases}/two_steps"
     rec = d.get(precision, {}).get(key)
     if not rec or rec.get("source_hash") != kernel_source_hash():
         return None
@@ -158,11 +166,11 @@ def run_batch(specs, precision, steps, warmup, config=None):
     finite = all(d[2] == 0 for d in diags)
     b.close()
     nodes = sum(s.nr * s.nz for s in specs)
-    kernel_ms = ev_ms / k
+    step_ms, kernel_ms = ev_ms / k, ev_ms / k * STEPS_PER_LAUNCH[precision]
     note(f"batch {len(specs)} x {specs[0].nr}x{specs[0].nz} {precision} {specs[0].collision} config {config}: "
-         f"{kernel_ms * 1e3:.2f} us per step, {nodes * k / wall / 1e6:.0f} MLUPS")
+         f"{step_ms * 1e3:.2f} us per step, {nodes * k / wall / 1e6:.0f} MLUPS")
     bytes_launch = nodes * BYTES_PER_LU[precision]
-    return {"mlups": nodes * k / wall / 1e6, "ms_per_step": wall / k * 1e3, "kernel_ms": kernel_ms,
+    return {"mlups": nodes * k / wall / 1e6, "ms_per_step": wall / k * 1e3, "kernel_ms": kernel_ms, "step_ms": step_ms,
             "achieved_GBs": bytes_launch / (kernel_ms * 1e-3) / 1e9, "bytes_per_launch": bytes_launch,
             "steps": k, "config": {"tile_rows": config[0], "persistent": config[1], "schedule": config[2],
                                    "bands": config[3]},
@@ -212,7 +220,7 @@ def run_single(spec, precision, steps, warmup):
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     nodes = spec.nr * spec.nz
-    kernel_ms = start.elapsed_time(end) / steps
+    kernel_ms = start.elapsed_time(end) / steps * STEPS_PER_LAUNCH[precision]
     return {"mlups": nodes * steps / wall / 1e6, "kernel_ms": kernel_ms,
             "achieved_GBs": nodes * BYTES_PER_LU[precision] / (kernel_ms * 1e-3) / 1e9, "tile_rows": tile}
 
@@ -360,7 +368,8 @@ def main():
                      "unit": "GB/s", "frac": round(main_res["achieved_GBs"] / HBM_PEAK_GBS, 4),
                      "traffic": (None if stochastic else
                                  measured_traffic(args.precision, main_res["config"], args.cases)),
-                     "kernel": "batch_step_kernel",
+                     "kernel": "batch_step_kernel_h" if args.precision == "fp16" else "batch_pair_kernel",
+                     "steps_per_launch": STEPS_PER_LAUNCH[args.precision],
                      "kernel_ms_mean": round(main_res["kernel_ms"], 5),
                      "bytes_per_launch": main_res["bytes_per_launch"],
                      "copy_GBs": round(copy_gbs, 1), "frac_of_copy": round(main_res["achieved_GBs"] / copy_gbs, 4)},
@@ -377,8 +386,8 @@ def main():
             line["variants"][f"batch_{other}"] = {
                 "mlups": round(ob["mlups"], 1), "frac": round(ob["achieved_GBs"] / HBM_PEAK_GBS, 4),
                 "frac_of_copy": round(ob["achieved_GBs"] / copy_gbs, 4),
-                "kernel_ms_mean": round(ob["kernel_ms"], 5), "bytes_per_lu": BYTES_PER_LU[other],
-                "moved_bytes_per_lu": MOVED_BYTES_PER_LU[other], **ob["config"]}
+                "kernel_ms_mean": round(ob["kernel_ms"], 5), "bytes_per_lu": BYTES_PER_LU[other] / STEPS_PER_LAUNCH[other],
+                "moved_bytes_per_lu": MOVED_BYTES_PER_LU[other] / STEPS_PER_LAUNCH[other], **ob["config"]}
         # the same batch at a quarter of the cases (411 MB in FP32), launch
         # configuration of the full batch
         if args.cases >= 32:
@@ -387,9 +396,9 @@ def main():
             line["variants"][f"batch_{args.precision}_{args.cases // 4}cases"] = {
                 "mlups": round(ob["mlups"], 1), "frac": round(ob["achieved_GBs"] / HBM_PEAK_GBS, 4),
                 "kernel_ms_mean": round(ob["kernel_ms"], 5),
-                "us_per_mlu": round(ob["kernel_ms"] * 1e3 / (sum(q.nr * q.nz for q in qs) / 1e6), 4),
+                "us_per_mlu": round(ob["step_ms"] * 1e3 / (sum(q.nr * q.nz for q in qs) / 1e6), 4),
                 "cases": args.cases // 4, **ob["config"]}
-            line["roofline"]["us_per_mlu"] = round(main_res["kernel_ms"] * 1e3 / (nodes * args.cases / 1e6), 4)
+            line["roofline"]["us_per_mlu"] = round(main_res["step_ms"] * 1e3 / (nodes * args.cases / 1e6), 4)
         # the other collision forms on the same batch, each precision's launch configuration
         for form in ("srt", "nmrt"):
             fspecs = batch_specs(args.cases)

@@ -162,7 +162,7 @@ int lbm_axi_init(const lbm_axi_params *params, void *dev_state, size_t dev_bytes
 
 /* Enqueues nsteps >= 0 time steps (Eqs. 9-40, Sec. 2.2-2.3) on the case's
  * stream and returns without waiting.  One kernel launch per step, or per two
- * steps for large FP64 and FP32 cases (never while the stream is recorded into
+ * steps for FP64 and FP32 cases (never while the stream is recorded into
  * a graph); the results are the same bits. */
 int lbm_axi_step(lbm_axi_case *c, int64_t nsteps);
 
@@ -252,7 +252,8 @@ int lbm_axi_batch_admit(lbm_axi_batch *b, const lbm_axi_params *params, const do
                         int64_t nsteps, int32_t *slot);
 
 /* Advances every running case by min(chunk_steps, its remaining steps):
- * one launch per step; cases that reach their step count stop there.
+ * one launch per step, or per two steps in FP64 and FP32 storage; cases that
+ * reach their step count stop there.
  * Asynchronous: a change in the set of running cases re-uploads the case
  * table and work list through a pinned staging buffer, ordered on the stream
  * after the steps already enqueued.  A run of chunk_steps steps over an

@@ -6,7 +6,7 @@ without the HIP library or a GPU:
   inputs  seeded case parameters and initial phase fields
   abi     ctypes binding of liblbm_axi.so (include/lbm_axi.h)
   case    AxiCase: one device-resident case (torch for memory and streams)
-  batch   Batch: many cases advanced by one launch per step
+  batch   Batch: many cases advanced together by each launch
   build   hipcc build of liblbm_axi.so
 """
 import importlib

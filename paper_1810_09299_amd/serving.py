@@ -3,7 +3,7 @@ and step counts arriving over time).
 
 A request is admitted as soon as it has arrived and the batch has a free slot
 and a pool block large enough for its state (admission by HBM footprint, in
-arrival order); admitted requests advance together, one fused launch per step
+arrival order); admitted requests advance together, in fused launches
 for all of them, in chunks of `chunk` steps replayed from a hipGraph; a request
 that reaches its step count is read back (fields and diagnostics at its final
 time) and released, freeing its slot and memory for the next arrivals.
