@@ -162,8 +162,12 @@ int lbm_axi_init(const lbm_axi_params *params, void *dev_state, size_t dev_bytes
 
 /* Enqueues nsteps >= 0 time steps (Eqs. 9-40, Sec. 2.2-2.3) on the case's
  * stream and returns without waiting.  One kernel launch per step, or per two
- * steps for FP64 and FP32 cases (never while the stream is recorded into
- * a graph); the results are the same bits. */
+ * steps for FP64 and FP32 cases (never while the stream is recorded into a
+ * graph); the results are the same bits.
+ * A graph recorded from the stream starts, at each replay, from the buffer of
+ * the state that was current at the recording.  An even number of steps,
+ * recorded or enqueued live, leaves the state in the buffer it came from, so
+ * that replays and live steps may follow each other. */
 int lbm_axi_step(lbm_axi_case *c, int64_t nsteps);
 
 /* Fields at the current time t (phi of Eq. 16, rho of Eq. 17, u of Eq. 32, p of

@@ -39,6 +39,7 @@ struct lbm_axi_case {
     int tile_r;
     int cus;               // compute units of the device
     axi::TwoStepPlan two;  // of the case's own launches
+    bool recorded;         // a caller's graph holds steps or a read-back of it (pairs_of)
     int device;            // HIP device the case was initialised on
     axi::Geom geom;             // geometry of the step launch (tiles for tile_r)
     axi::Phys<double> P64;
@@ -62,6 +63,14 @@ int pair_strips(int nz, int z_periodic, int waves);
 // two steps per launch for the n cases of one launch: the plan that suits them
 // (singly: one case, which may also step singly)
 TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool singly);
+// whether what is enqueued on the stream now is being recorded into a graph
+bool recording(hipStream_t stream);
+// how many of n steps go in pairs.  A graph holds the addresses of the buffer
+// that was current when it was recorded, and a replay starts there: what is
+// recorded (rec) goes singly, so that 2 m steps end in the buffer they began
+// in, and from then on (recorded) n steps enqueued live leave the buffer where
+// n single steps would, which an even number of pairs does.
+inline int64_t pairs_of(int64_t n, bool rec, bool recorded) { return rec ? 0 : (recorded ? n / 4 * 2 : n / 2); }
 // FP16-deviation storage: buffers of ping-pong side b, and the step from side cur
 struct HalfBuf {
     float *f0;       // f_0 plane (FP32)

@@ -960,26 +960,19 @@ void launch_two(lbm_axi_case *c, const Phys<R> &P)
         go(std::integral_constant<int, COLLIDE_MRT>{});
 }
 
-// Whether the steps enqueued now are being recorded into a graph.  A replay
-// starts from the buffer the recording started from, so a recorded run of
-// 2 m steps has to end in that buffer: two steps per launch would not always.
-bool recording(hipStream_t stream)
-{
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
-}
-
 int do_steps(lbm_axi_case *c, int64_t n)
 {
-    if (n >= 2 && c->prm.precision != LBM_AXI_FP16D && c->two.tile >= 0 && !recording(c->stream)) {
-        for (; n >= 2; n -= 2) {
-            if (c->prm.precision == LBM_AXI_FP64)
-                launch_two<double, double>(c, c->P64);
-            else
-                launch_two<float, float>(c, c->P32);
-            c->cur ^= 1;
-            c->t += 2;
-        }
+    const bool rec = n > 0 && recording(c->stream);
+    c->recorded = c->recorded || rec;
+    int64_t pairs = 0;
+    if (c->prm.precision != LBM_AXI_FP16D && c->two.tile >= 0) pairs = pairs_of(n, rec, c->recorded);
+    for (n -= 2 * pairs; pairs > 0; --pairs) {
+        if (c->prm.precision == LBM_AXI_FP64)
+            launch_two<double, double>(c, c->P64);
+        else
+            launch_two<float, float>(c, c->P32);
+        c->cur ^= 1;
+        c->t += 2;
     }
     for (int64_t s = 0; s < n; ++s) {
         if (c->prm.precision == LBM_AXI_FP64)
@@ -1039,6 +1032,12 @@ unsigned blocks_for(int64_t n, int threads) { return (unsigned)((n + threads - 1
 } // namespace
 
 namespace axi {
+bool recording(hipStream_t stream)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+}
+
 int pair_strips(int nz, int z_periodic, int waves)
 {
     const int lanes = 64 * waves, inner = lanes - 2 * PAIR_HALO;
@@ -1338,6 +1337,7 @@ int lbm_axi_init(const lbm_axi_params *params, void *dev_state, size_t dev_bytes
     c->bytes = dev_bytes;
     c->t = 0;
     c->cur = 0;
+    c->recorded = false;
     c->cus = 256;
     (void)hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev);
     c->tile_r = default_tile(c);
@@ -1415,6 +1415,7 @@ int lbm_axi_moments_noalloc(lbm_axi_case *c, double *phi, double *rho, double *u
     if ((int64_t)c->prm.nr * c->prm.nz > ((int64_t)1 << 25)) return LBM_AXI_EINVAL;
     double *sc = nullptr;
     if (noalloc_scratch(c->device, &sc) != LBM_AXI_OK) return LBM_AXI_EDEVICE;
+    c->recorded = c->recorded || recording(c->stream);
     return run_readback(c, Fields{phi, rho, uz, ur, p}, sc, diag);
 }
 

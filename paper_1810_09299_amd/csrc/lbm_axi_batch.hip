@@ -216,7 +216,8 @@ struct lbm_axi_batch {
     int schedule;                       // bit 0: largest case first (else admission order); bit 1: contiguous bands per XCD
     int bands;                          // contiguous tile bands per case (multiple of 8)
     int cu_count;
-    int phase;                          // buffer phase of the next step (flips every step)
+    int phase;                          // buffer phase of the next launch (flips every launch)
+    bool recorded;                      // a caller's graph holds steps of it (pairs_of)
     int64_t since_upload;               // steps launched since the case table was uploaded
     bool table_ramp;                    // the uploaded table has a case still ramping its gravity
     // device areas in the pool head
@@ -243,7 +244,7 @@ struct lbm_axi_batch {
     int mode_start[NCLASS + 1];         // items of class q: [mode_start[q], mode_start[q + 1])
     std::vector<int> running;           // slots in the work list
     bool dirty;                         // work list / descriptors must be rebuilt
-    std::map<int, hipGraphExec_t> graphs;   // by 2 * run length + starting phase
+    std::map<int64_t, hipGraphExec_t> graphs;   // by run length, phase and `recorded`
     std::vector<Retired> retired;
     int64_t launches;
 };
@@ -654,17 +655,20 @@ void launch_pairs(lbm_axi_batch *b, int parity, int step)
     launch_pair_part<T, R, COLLIDE_NMRT>(b, parity, step);
 }
 
-// launches that n steps take: two steps each where the running cases have a
-// list for it, the odd one alone (every launch flips the buffer phase)
-int launches_of(const lbm_axi_batch *b, int n) { return b->pair_work.empty() ? n : n / 2 + (n & 1); }
+// pairs that n steps take: where the running cases have a list for them (every
+// launch flips the buffer phase).  rec: a caller is recording the launches.
+int batch_pairs(const lbm_axi_batch *b, int n, bool rec)
+{
+    return b->pair_work.empty() ? 0 : (int)pairs_of(n, rec, b->recorded);
+}
 
-// n steps starting at buffer phase `phase`, the first `first` steps after the
-// table upload
-void launch_steps(lbm_axi_batch *b, int n, int phase, int64_t first)
+// n steps, 2 * pairs of them in pairs, starting at buffer phase `phase`, the
+// first `first` steps after the table upload
+void launch_steps(lbm_axi_batch *b, int n, int pairs, int phase, int64_t first)
 {
     int parity = phase & 1;
     int s = 0;
-    for (; !b->pair_work.empty() && s + 2 <= n; s += 2, parity ^= 1) {
+    for (; s < 2 * pairs; s += 2, parity ^= 1) {
         const int step = (int)std::min<int64_t>(first + s, INT32_MAX - 1);
         if (b->precision == LBM_AXI_FP64)
             launch_pairs<double, double>(b, parity, step);
@@ -685,13 +689,14 @@ void launch_steps(lbm_axi_batch *b, int n, int phase, int64_t first)
 // the graph of n steps from the current phase, captured if not yet seen
 int graph_for(lbm_axi_batch *b, int n, int phase, hipGraphExec_t *out)
 {
-    const int key = 2 * n + phase;
+    // run length, starting phase, and whether a recording keeps the pairs even
+    const int64_t key = 4 * (int64_t)n + 2 * (b->recorded ? 1 : 0) + phase;
     auto it = b->graphs.find(key);
     if (it == b->graphs.end()) {
         hipGraph_t graph;
         if (hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
             return LBM_AXI_EDEVICE;
-        launch_steps(b, n, phase, 0);   // no case of the table ramps: the step count is unused
+        launch_steps(b, n, batch_pairs(b, n, false), phase, 0);   // no case of the table ramps: the step count is unused
         if (hipStreamEndCapture(b->stream, &graph) != hipSuccess) return LBM_AXI_EDEVICE;
         hipGraphExec_t exec;
         if (hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess) {
@@ -710,19 +715,26 @@ int graph_for(lbm_axi_batch *b, int n, int phase, hipGraphExec_t *out)
 int run_span(lbm_axi_batch *b, int n, bool use_graph)
 {
     if (n <= 0 || b->work.empty()) return LBM_AXI_OK;
-    if (use_graph && !b->table_ramp) {
+    const bool replay = use_graph && !b->table_ramp;
+    const bool rec = !replay && recording(b->stream);
+    if (rec) {
+        b->recorded = true;
+        for (int s : b->running) b->cases[s]->recorded = true;
+    }
+    const int pairs = batch_pairs(b, n, rec);
+    if (replay) {
         hipGraphExec_t exec;
         int rc = graph_for(b, n, b->phase, &exec);
         if (rc) return rc;
         if (hipGraphLaunch(exec, b->stream) != hipSuccess) return LBM_AXI_EDEVICE;
     } else {
-        launch_steps(b, n, b->phase, b->since_upload);
+        launch_steps(b, n, pairs, b->phase, b->since_upload);
         if (hipGetLastError() != hipSuccess) return LBM_AXI_EDEVICE;
     }
     b->launches += n;
     b->since_upload += n;
     // host bookkeeping: time, remaining steps, buffer of every running case
-    const int flip = launches_of(b, n) & 1;
+    const int flip = (n - pairs) & 1;
     b->phase ^= flip;
     bool still_ramping = false;
     for (int s : b->running) {
@@ -816,6 +828,7 @@ int lbm_axi_batch_create(void *dev_pool, size_t pool_bytes, int32_t max_cases, i
     b->schedule = 1;
     b->bands = DEFAULT_BANDS;
     b->phase = 0;
+    b->recorded = false;
     b->since_upload = 0;
     b->table_ramp = false;
     b->stage_next = 0;

@@ -116,3 +116,87 @@ def test_recorded_steps_replay_from_their_own_result(nr, nz):
     for x, y in zip(ref[:3], c.get_state()[:3]):
         assert np.array_equal(x, y)
     c.close()
+
+
+FIELDS = ("phi", "rho", "uz", "ur", "p")
+
+
+@pytest.mark.parametrize("precision,nr,nz", [("fp64", 64, 128), ("fp32", 64, 128), ("fp16", 64, 128),
+                                             ("fp64", 601, 2003), ("fp32", 601, 2003)])
+def test_live_steps_between_replays(precision, nr, nz):
+    """A replay starts from the buffer that was current when its steps, or its
+    read-back, were recorded: live steps, in tiles and marching, leave the state
+    there after any even number of them."""
+    import torch
+    from paper_1810_09299_amd import abi
+    from paper_1810_09299_amd.case import AxiCase
+    spec = _spec(nr, nz, True, "mrt")
+    spec.g_ramp = 0.0
+    stream = torch.cuda.Stream()
+    c = AxiCase(spec, precision=precision, stream=stream)
+    ref = AxiCase(spec, precision=precision)
+    c.step(6)                                         # before the recording: three pairs, buffer 1
+    out = [torch.empty((nr, nz), dtype=torch.float64, device="cuda") for _ in FIELDS]
+    diag = torch.empty(64, dtype=torch.float64, device="cuda")
+    steps, read = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(read, stream=stream):
+        abi.lbm_axi_moments_noalloc(c.handle, *(o.data_ptr() for o in out), diag.data_ptr())
+    with torch.cuda.graph(steps, stream=stream):
+        c.step(2)
+    done = 6
+    for live in ((2,), (6,), (50,), (3, 5), (0,), (7, 1, 2)):
+        steps.replay()
+        torch.cuda.synchronize()
+        for n in live:
+            c.step(n)
+        done += 2 + sum(live)
+        while ref.t < done:
+            ref.step(1)
+        want = ref.moments()[0]
+        read.replay()
+        torch.cuda.synchronize()
+        got = c.moments()[0]
+        for o, k in zip(out, FIELDS):
+            assert np.array_equal(o.cpu().numpy(), want[k]), (live, k)
+            assert np.array_equal(got[k], want[k]), (live, k)
+    for x, y in zip(ref.get_state()[:3], c.get_state()[:3]):
+        assert np.array_equal(x, y)
+    c.close()
+    ref.close()
+
+
+def test_recorded_batch_steps_replay_from_their_own_result():
+    """Steps of a batch that a caller records (launched one by one: a gravity
+    ramp), replayed between live ones, against a case in the same sequence."""
+    import torch
+    from paper_1810_09299_amd.batch import Batch
+    from paper_1810_09299_amd.case import AxiCase
+    spec = _spec(33, 130, True, "mrt")
+    spec.g_ramp = 1000.0
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    b = Batch(pool_bytes=Batch.pool_for([spec], "fp32"), max_cases=1, precision="fp32", stream=streams[0])
+    slot = b.admit(spec, 10 ** 6)
+    c = AxiCase(spec, precision="fp32", stream=streams[1])
+    b.run(4)
+    for _ in range(4):
+        c.step(1)
+    b.sync()
+    graphs = []
+    for step, stream in ((b.run, streams[0]), (c.step, streams[1])):
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            step(2)
+        graphs.append(g)
+    for live in ((2,), (6,), (1, 3), (50,)):
+        for g in graphs:
+            for _ in range(2):
+                g.replay()
+                torch.cuda.synchronize()
+        for n in live:
+            b.run(n)
+            for _ in range(n):
+                c.step(1)
+        for x, y in zip(b.get_state(slot)[:3], c.get_state()[:3]):
+            assert np.array_equal(x, y), live
+    b.close()
+    c.close()
