@@ -1035,7 +1035,11 @@ namespace axi {
 bool recording(hipStream_t stream)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    // the null stream cannot be recorded, but asking about it while a blocking
+    // stream is recorded is an error, which the next launch check would report
+    (void)hipGetLastError();
+    return false;
 }
 
 int pair_strips(int nz, int z_periodic, int waves)

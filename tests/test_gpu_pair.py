@@ -200,3 +200,30 @@ def test_recorded_batch_steps_replay_from_their_own_result():
             assert np.array_equal(x, y), live
     b.close()
     c.close()
+
+
+def test_steps_on_the_null_stream_while_another_stream_records():
+    """A program records a graph of its own on a blocking stream; a case on the
+    null stream goes on stepping, in pairs and singly."""
+    import ctypes
+
+    import torch
+    from paper_1810_09299_amd.case import AxiCase
+    hip = ctypes.CDLL("libamdhip64.so")
+    spec = _spec(64, 128, True, "mrt")
+    c = AxiCase(spec, precision="fp32", stream=torch.cuda.default_stream())
+    assert c.stream.cuda_stream == 0
+    s, g = ctypes.c_void_p(), ctypes.c_void_p()
+    assert hip.hipStreamCreate(ctypes.byref(s)) == 0
+    assert hip.hipStreamBeginCapture(s, 2) == 0       # hipStreamCaptureModeRelaxed
+    try:
+        for n in (2, 1, 4):
+            c.step(n)
+    finally:
+        assert hip.hipStreamEndCapture(s, ctypes.byref(g)) == 0
+    if g.value:
+        assert hip.hipGraphDestroy(g) == 0
+    assert hip.hipStreamDestroy(s) == 0
+    for x, y in zip(_single_steps(spec, "fp32", 7)[:3], c.get_state()[:3]):
+        assert np.array_equal(x, y)
+    c.close()
