@@ -6,8 +6,9 @@
 //   pop[2][2][9][plane]  ping-pong x {f, g} x populations, storage type T
 //   aux[3][plane]        previous-step phi, u_z, u_r (T) of buffer 0
 //   fld[5][plane]        doubles: the aux of buffer 1 (T) in the first planes,
-//                        the last for state transfer; with FP16-deviation
-//                        storage (axi_half.hpp) the moments fields
+//                        the last two for the moments fields of a case that
+//                        a graph holds, the last for state transfer; with
+//                        FP16-deviation storage (axi_half.hpp) the moments fields
 //   red[...]             double scratch for the diagnostics reductions
 // plane = nr*nz rounded up to 64 elements, plus 64; SoA, z fastest.
 //   diag                 the diagnostics record (lbm_axi_diag) reduced on the device
@@ -493,11 +494,11 @@ __global__ __launch_bounds__(TZ *TR) void moments_kernel(Geom g, Phys<R> P, cons
             R r = (R)j + (R)0.5, ir = inv_radius<R>(j);
             Macro<R> m;
             macro_state<FORM_OF_P>(P, r, ir, st, gv, uzp, urp, m);
-            F.phi[n] = (double)m.phi;
-            F.rho[n] = (double)m.rho;
-            F.uz[n] = (double)m.uz;
-            F.ur[n] = (double)m.ur;
-            F.p[n] = (double)m.p;
+            if (F.phi) F.phi[n] = (double)m.phi;
+            if (F.rho) F.rho[n] = (double)m.rho;
+            if (F.uz) F.uz[n] = (double)m.uz;
+            if (F.ur) F.ur[n] = (double)m.ur;
+            if (F.p) F.p[n] = (double)m.p;
             double mass = 0.0;
 #pragma unroll
             for (int i = 0; i < 9; ++i) mass += (double)fv[i];
@@ -1000,15 +1001,11 @@ Fields case_fields(const lbm_axi_case *c)
     return Fields{f, f + pl, f + 2 * pl, f + 3 * pl, f + 4 * pl};
 }
 
-// The read-back of a case: fields into F, the diagnostics record into the
-// device record `out`; `scratch` holds the reductions' partials
-// (DIAG_SCRATCH_DOUBLES doubles; nothing in it needs to start at zero).
-int run_readback(lbm_axi_case *c, const Fields &F, double *scratch, lbm_axi_diag *out)
+// the macroscopic prefix of the step from time t: the fields that F asks for
+// (FP16-deviation storage: all), and the sums' partials
+void launch_moments(lbm_axi_case *c, const Geom &g, const Fields &F, double *scratch)
 {
-    const Geom g = geom_for(c, MOM_TR);
-    const int gas = c->prm.dispersed_gas;
-    const int nb = moments_blocks(g);
-    // the fields at time t: the prefix of the step from t, with its acceleration
+    const int nb = moments_blocks(g), gas = c->prm.dispersed_gas;
     if (c->prm.precision == LBM_AXI_FP64)
         moments_kernel<double, double, MOM_TR><<<nb, TZ * MOM_TR, 0, c->stream>>>(
             g, phys_at(c->P64, c->t), (const double *)c->pop[c->cur][0], (const double *)c->pop[c->cur][1],
@@ -1020,6 +1017,17 @@ int run_readback(lbm_axi_case *c, const Fields &F, double *scratch, lbm_axi_diag
         moments_kernel<float, float, MOM_TR><<<nb, TZ * MOM_TR, 0, c->stream>>>(
             g, phys_at(c->P32, c->t), (const float *)c->pop[c->cur][0], (const float *)c->pop[c->cur][1],
             (const float *)c->aux[c->cur], F, gas, scratch);
+}
+
+// The read-back of a case: fields into F (phi and p at least), the diagnostics
+// record into the device record `out`; `scratch` holds the reductions' partials
+// (DIAG_SCRATCH_DOUBLES doubles; nothing in it needs to start at zero).
+int run_readback(lbm_axi_case *c, const Fields &F, double *scratch, lbm_axi_diag *out)
+{
+    const Geom g = geom_for(c, MOM_TR);
+    const int gas = c->prm.dispersed_gas;
+    const int nb = moments_blocks(g);
+    launch_moments(c, g, F, scratch);
     const int64_t nn = (int64_t)g.nr * g.nz;
     const int np = (int)std::min<int64_t>(PRS_BLOCKS, (nn + DIAG_THREADS - 1) / DIAG_THREADS);
     diag_pressure<<<np, DIAG_THREADS, 0, c->stream>>>(g, gas, c->prm.W, F, nb, scratch);
@@ -1394,15 +1402,37 @@ int lbm_axi_moments(lbm_axi_case *c, double *phi, double *rho, double *uz, doubl
                     lbm_axi_diag *diag)
 {
     if (!c) return LBM_AXI_ESTATE;
-    const Fields F = case_fields(c);
-    int rc = run_readback(c, F, c->part, c->diag);
-    if (rc) return rc;
-    int64_t nn = (int64_t)c->prm.nr * c->prm.nz;
-    double *outs[5] = {phi, rho, uz, ur, p};
-    const double *planes[5] = {F.phi, F.rho, F.uz, F.ur, F.p};
-    for (int q = 0; q < 5; ++q)
-        if (outs[q])
-            HIP_OK(hipMemcpyAsync(outs[q], planes[q], nn * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    const int64_t nn = (int64_t)c->prm.nr * c->prm.nz, pl = c->geom.plane;
+    auto copy_out = [&](double *out, const double *plane) {
+        return out ? hipMemcpyAsync(out, plane, nn * sizeof(double), hipMemcpyDeviceToHost, c->stream) : hipSuccess;
+    };
+    if (c->recorded && c->prm.precision != LBM_AXI_FP16D) {
+        // a graph may hold a state in either population buffer: the fields go
+        // through the two planes that nothing else keeps, two at a time
+        double *const a = c->xfer - pl, *const b = c->xfer;
+        const Geom g = geom_for(c, MOM_TR);
+        int rc = run_readback(c, Fields{a, nullptr, nullptr, nullptr, b}, c->part, c->diag);
+        if (rc) return rc;
+        HIP_OK(copy_out(phi, a));
+        HIP_OK(copy_out(p, b));
+        if (rho || uz) {
+            launch_moments(c, g, Fields{nullptr, a, b, nullptr, nullptr}, c->part);
+            HIP_OK(copy_out(rho, a));
+            HIP_OK(copy_out(uz, b));
+        }
+        if (ur) {
+            launch_moments(c, g, Fields{nullptr, nullptr, nullptr, a, nullptr}, c->part);
+            HIP_OK(copy_out(ur, a));
+        }
+        if (launch_ok()) return LBM_AXI_EDEVICE;
+    } else {
+        const Fields F = case_fields(c);
+        int rc = run_readback(c, F, c->part, c->diag);
+        if (rc) return rc;
+        double *outs[5] = {phi, rho, uz, ur, p};
+        const double *planes[5] = {F.phi, F.rho, F.uz, F.ur, F.p};
+        for (int q = 0; q < 5; ++q) HIP_OK(copy_out(outs[q], planes[q]));
+    }
     lbm_axi_diag d;
     HIP_OK(hipMemcpyAsync(&d, c->diag, sizeof(lbm_axi_diag), hipMemcpyDeviceToHost, c->stream));
     HIP_OK(hipStreamSynchronize(c->stream));

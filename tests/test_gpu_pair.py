@@ -227,3 +227,36 @@ def test_steps_on_the_null_stream_while_another_stream_records():
     for x, y in zip(_single_steps(spec, "fp32", 7)[:3], c.get_state()[:3]):
         assert np.array_equal(x, y)
     c.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16"])
+def test_read_back_between_replays_of_single_steps(precision):
+    """Two graphs of one step each, one per buffer, replayed in turn: a live
+    read-back in between (of the other buffer, in which the first graph began)
+    leaves the state that the second begins with."""
+    import torch
+    from paper_1810_09299_amd.case import AxiCase
+    spec = _spec(33, 130, True, "mrt")
+    spec.g_ramp = 0.0
+    stream = torch.cuda.Stream()
+    c = AxiCase(spec, precision=precision, stream=stream)
+    graphs = [torch.cuda.CUDAGraph() for _ in range(2)]
+    for g in graphs:
+        with torch.cuda.graph(g, stream=stream):
+            c.step(1)
+    for _ in range(3):
+        for g in graphs:
+            g.replay()
+            torch.cuda.synchronize()
+            last = c.moments()[0]
+            c.diagnostics()
+    ref = AxiCase(spec, precision=precision)
+    for _ in range(6):
+        ref.step(1)
+    want = ref.moments()[0]
+    for k in FIELDS:
+        assert np.array_equal(last[k], want[k]), k
+    for x, y in zip(ref.get_state()[:3], c.get_state()[:3]):
+        assert np.array_equal(x, y)
+    c.close()
+    ref.close()
