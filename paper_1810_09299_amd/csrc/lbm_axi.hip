@@ -1065,7 +1065,9 @@ int pair_strips(int nz, int z_periodic, int waves)
 // once (or the fewest times), a run costing about 10 rows more than it owns:
 // its start and the rows recomputed at its ends (512 x 2048 in FP32: runs of 8
 // rows 30.8 us a step, of 12 31.2, of 32 over 35; the 64 cases: 4 runs 155.8, 6
-// runs 185, 8 runs 164.8).
+// runs 185, 8 runs 164.8).  Tall and narrow cases have many runs: 19200 x 64
+// takes 27.9 us in them, 90 in 256 runs, 44.7 singly; 300000 x 4 194, 1275 and
+// 284.
 static void plan_march(const lbm_axi_case *const *cases, int n, TwoStepPlan &best)
 {
     const bool fp64 = cases[0]->prm.precision == LBM_AXI_FP64, unit = cases[0]->P64.mode == COLLIDE_MRT_UNIT;
@@ -1092,11 +1094,8 @@ static void plan_march(const lbm_axi_case *const *cases, int n, TwoStepPlan &bes
     }
     const int64_t slots = (int64_t)cases[0]->cus * (resident / best.waves);
     int64_t best_cost = 0;
-    int last = 0;
-    for (int c = 1; c <= 256; ++c) {
-        const int rows = std::max(4, (max_nr + c - 1) / c);
-        if (rows == last) continue;
-        last = rows;
+    // every length that a number of equal runs of the tallest case has, from one run on
+    for (int rows = max_nr;;) {
         int64_t groups = 0;
         for (int i = 0; i < n; ++i)
             groups += (int64_t)pair_strips(cases[i]->prm.nz, cases[i]->prm.z_periodic, best.waves) *
@@ -1106,6 +1105,9 @@ static void plan_march(const lbm_axi_case *const *cases, int n, TwoStepPlan &bes
             best_cost = cost;
             best.rows = rows;
         }
+        if (rows <= 4) break;
+        const int runs = (max_nr + rows - 2) / (rows - 1);
+        rows = std::max(4, (max_nr + runs - 1) / runs);
     }
 }
 

@@ -1,0 +1,26 @@
+// Prints how launches of two steps would go (two_step_plan) on a device of 256
+// compute units.  One launch per line of input: singly (0/1), FP64 (0/1),
+// collision form (COLLIDE_*), the number of cases, then nr, nz, z_periodic of each.
+#include "../paper_1810_09299_amd/csrc/case_internal.hpp"
+
+#include <cstdio>
+#include <vector>
+
+int main()
+{
+    int singly, fp64, mode, n;
+    while (scanf("%d %d %d %d", &singly, &fp64, &mode, &n) == 4) {
+        std::vector<lbm_axi_case> cases(n);
+        std::vector<const lbm_axi_case *> ptrs;
+        for (lbm_axi_case &c : cases) {
+            if (scanf("%d %d %d", &c.prm.nr, &c.prm.nz, &c.prm.z_periodic) != 3) return 1;
+            c.prm.precision = fp64 ? LBM_AXI_FP64 : LBM_AXI_FP32;
+            c.P64.mode = c.P32.mode = mode;
+            c.cus = 256;
+            ptrs.push_back(&c);
+        }
+        const axi::TwoStepPlan p = axi::two_step_plan(ptrs.data(), n, singly != 0);
+        printf("%d %d %d %d\n", (int)p.march, p.waves, p.rows, p.tile);
+    }
+    return 0;
+}
