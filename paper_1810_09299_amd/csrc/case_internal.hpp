@@ -61,8 +61,8 @@ int64_t plane_elems(int nr, int nz);
 // how many strips `waves` wavefronts cut nz columns into (axi_pair.hpp)
 int pair_strips(int nz, int z_periodic, int waves);
 // two steps per launch for the n cases of one launch: the plan that suits them
-// (singly: one case, which may also step singly)
-TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool singly);
+// (alone: the one case's own launch, which may also step singly; else a batch's)
+TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool alone);
 // whether what is enqueued on the stream now is being recorded into a graph
 bool recording(hipStream_t stream);
 // how many of n steps go in pairs.  A graph holds the addresses of the buffer

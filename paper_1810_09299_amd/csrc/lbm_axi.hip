@@ -1061,14 +1061,16 @@ int pair_strips(int nz, int z_periodic, int waves)
 // that only hold a halo cost what the others do: 64 cases of 512 columns in
 // FP32 took 155.8 us a step in one strip of 8 wavefronts, 167 in three of 3, 219
 // in ten of 1; strips that share lines cost 3 % more), the smallest of equals;
-// then the shortest runs of rows that fill the device's resident wavefronts
-// once (or the fewest times), a run costing about 10 rows more than it owns:
+// then the shortest runs of rows that fill the resident wavefronts of the
+// fullest XCD once (or the fewest times), a run costing about 10 rows more than it owns:
 // its start and the rows recomputed at its ends (512 x 2048 in FP32: runs of 8
 // rows 30.8 us a step, of 12 31.2, of 32 over 35; the 64 cases: 4 runs 155.8, 6
 // runs 185, 8 runs 164.8).  Tall and narrow cases have many runs: 19200 x 64
 // takes 27.9 us in them, 90 in 256 runs, 44.7 singly; 300000 x 4 194, 1275 and
-// 284.
-static void plan_march(const lbm_axi_case *const *cases, int n, TwoStepPlan &best)
+// 284.  A batch deals whole runs to the XCDs (build_pairs): ten FP64 cases of
+// 256 x 512 fill every XCD but two once in 10 runs each, those two and so the
+// launch twice (105 us a step, singly 83), and all once in 9.
+static void plan_march(const lbm_axi_case *const *cases, int n, bool alone, TwoStepPlan &best)
 {
     const bool fp64 = cases[0]->prm.precision == LBM_AXI_FP64, unit = cases[0]->P64.mode == COLLIDE_MRT_UNIT;
     // resident wavefronts per compute unit, by LDS (FP64: more than one per
@@ -1092,15 +1094,23 @@ static void plan_march(const lbm_axi_case *const *cases, int n, TwoStepPlan &bes
             best.waves = w;
         }
     }
-    const int64_t slots = (int64_t)cases[0]->cus * (resident / best.waves);
+    const int64_t slots = std::max(1, cases[0]->cus * (resident / best.waves) / 8);      // of one XCD
+    auto fullest_xcd = [&](int rows) {
+        int64_t groups[8] = {};
+        int next = 0;
+        for (int i = 0; i < n; ++i) {
+            const lbm_axi_params &p = cases[i]->prm;
+            const int strips = pair_strips(p.nz, p.z_periodic, best.waves), runs = (p.nr + rows - 1) / rows;
+            if (alone) return ((int64_t)strips * runs + 7) / 8;                          // xcd_tile
+            for (int x = 0; x < 8; ++x) groups[(next + x) % 8] += (int64_t)(runs / 8 + (x < runs % 8)) * strips;
+            next = (next + runs) % 8;
+        }
+        return *std::max_element(groups, groups + 8);
+    };
     int64_t best_cost = 0;
     // every length that a number of equal runs of the tallest case has, from one run on
     for (int rows = max_nr;;) {
-        int64_t groups = 0;
-        for (int i = 0; i < n; ++i)
-            groups += (int64_t)pair_strips(cases[i]->prm.nz, cases[i]->prm.z_periodic, best.waves) *
-                      ((cases[i]->prm.nr + rows - 1) / rows);
-        const int64_t cost = (groups + slots - 1) / slots * (rows + 10);
+        const int64_t cost = (fullest_xcd(rows) + slots - 1) / slots * (rows + 10);
         if (!best_cost || cost < best_cost) {
             best_cost = cost;
             best.rows = rows;
@@ -1136,7 +1146,7 @@ constexpr TileCost TILE_COST[2][TILE_SHAPES] = {
 };
 constexpr float SINGLE_COST[2] = {7.7f, 11.0f};
 
-TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool singly)
+TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool alone)
 {
     TwoStepPlan plan{false, 1, 4, 0};
     const bool fp64 = cases[0]->prm.precision == LBM_AXI_FP64;
@@ -1144,7 +1154,7 @@ TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool singly)
     for (int i = 0; i < n; ++i) nodes += (int64_t)cases[i]->prm.nr * cases[i]->prm.nz;
     plan.march = nodes >= (fp64 ? 800000 : 1200000);
     if (plan.march) {
-        plan_march(cases, n, plan);
+        plan_march(cases, n, alone, plan);
         return plan;
     }
     const int64_t cus = cases[0]->cus;
@@ -1163,7 +1173,7 @@ TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool singly)
             plan.tile = shape;
         }
     }
-    if (singly && best > SINGLE_COST[fp64 ? 1 : 0] && geom_for(cases[0], 8).tiles <= cus) plan.tile = -1;
+    if (alone && best > SINGLE_COST[fp64 ? 1 : 0] && geom_for(cases[0], 8).tiles <= cus) plan.tile = -1;
     return plan;
 }
 

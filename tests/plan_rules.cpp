@@ -1,5 +1,5 @@
 // Prints how launches of two steps would go (two_step_plan) on a device of 256
-// compute units.  One launch per line of input: singly (0/1), FP64 (0/1),
+// compute units.  One launch per line of input: alone (0/1), FP64 (0/1),
 // collision form (COLLIDE_*), the number of cases, then nr, nz, z_periodic of each.
 #include "../paper_1810_09299_amd/csrc/case_internal.hpp"
 
@@ -8,8 +8,8 @@
 
 int main()
 {
-    int singly, fp64, mode, n;
-    while (scanf("%d %d %d %d", &singly, &fp64, &mode, &n) == 4) {
+    int alone, fp64, mode, n;
+    while (scanf("%d %d %d %d", &alone, &fp64, &mode, &n) == 4) {
         std::vector<lbm_axi_case> cases(n);
         std::vector<const lbm_axi_case *> ptrs;
         for (lbm_axi_case &c : cases) {
@@ -19,7 +19,7 @@ int main()
             c.cus = 256;
             ptrs.push_back(&c);
         }
-        const axi::TwoStepPlan p = axi::two_step_plan(ptrs.data(), n, singly != 0);
+        const axi::TwoStepPlan p = axi::two_step_plan(ptrs.data(), n, alone != 0);
         printf("%d %d %d %d\n", (int)p.march, p.waves, p.rows, p.tile);
     }
     return 0;

@@ -23,8 +23,8 @@ def plan_of(tmp_path_factory):
                     f"-Wl,-rpath,{os.path.dirname(abi.LIB_PATH)}", "-o", exe],
                    check=True, capture_output=True, text=True, timeout=300)
 
-    def plan(precision, grids, singly=False, mode=UNIT):
-        line = f"{int(singly)} {int(precision == 'fp64')} {mode} {len(grids)} "
+    def plan(precision, grids, alone=False, mode=UNIT):
+        line = f"{int(alone)} {int(precision == 'fp64')} {mode} {len(grids)} "
         line += " ".join(f"{nr} {nz} {int(zper)}" for nr, nz, zper in grids)
         r = subprocess.run([exe], input=line, check=True, capture_output=True, text=True, timeout=60)
         march, waves, rows, tile = map(int, r.stdout.split())
@@ -37,8 +37,43 @@ def plan_of(tmp_path_factory):
 @pytest.mark.parametrize("nr,nz", [(9600, 128), (19200, 64), (75000, 16), (300000, 4), (2 ** 23, 4)])
 def test_tall_narrow_cases_fill_the_device(plan_of, precision, resident, nr, nz):
     """One strip: the runs of rows are what fills the device's resident wavefronts."""
-    p = plan_of(precision, [(nr, nz, True)], singly=True)
+    p = plan_of(precision, [(nr, nz, True)], alone=True)
     assert p["march"] and p["rows"] >= 4
     assert nz <= 64 * p["waves"]
     slots = 256 * (resident // p["waves"])
     assert -(-nr // p["rows"]) >= slots // 2
+
+
+def _strips(nz, zper, waves):
+    lanes = 64 * waves
+    if nz == lanes if zper else nz <= lanes:
+        return 1
+    return -(-nz // (lanes - 10))
+
+
+BATCHES = [[(256, 512, True)] * n for n in (7, 9, 10, 11, 16, 20, 33, 64)] + [
+    [(512, 2048, True), (32, 64, True)], [(300, 700, False)] * 5 + [(64, 300, True)] * 9,
+    [(200, 100, True), (90, 333, True)] * 31, [(128, 512, True)] * 13 + [(255, 509, False)] * 4]
+
+
+@pytest.mark.parametrize("precision,resident", [("fp32", 12), ("fp64", 4)])
+@pytest.mark.parametrize("grids", BATCHES)
+def test_march_of_a_batch_goes_by_its_fullest_xcd(plan_of, precision, resident, grids):
+    """Runs of rows go to the eight XCDs in turn, all strips of a run to one: no
+    other run length would have the fullest XCD done sooner (a run costs ten
+    rows beside its own)."""
+    p = plan_of(precision, grids)
+    if not p["march"]:
+        return
+
+    def cost(rows):
+        load, nxt = [0] * 8, 0
+        for nr, nz, zper in grids:
+            for _ in range(-(-nr // rows)):
+                load[nxt] += _strips(nz, zper, p["waves"])
+                nxt = (nxt + 1) % 8
+        return -(-max(load) // (32 * (resident // p["waves"]))) * (rows + 10)
+
+    tallest = max(g[0] for g in grids)
+    best = min(cost(-(-tallest // c)) for c in range(1, tallest // 4 + 1))
+    assert cost(p["rows"]) == min(best, cost(4))
