@@ -1137,12 +1137,18 @@ static void plan_march(const lbm_axi_case *const *cases, int n, bool alone, TwoS
 // unit and the smaller tiles of two steps, by their ragged edges, more, do they
 // stay ahead (69 x 1717 FP32: 7.7 against 8.5; 133 x 920 FP64, SRT: 11.5 against
 // 13.2), so a case steps singly there.
+// The general and the non-orthogonal MRT hold more registers: in FP64 a unit
+// takes one 16 x 16 tile of theirs at a time, two of the other forms' (256 x 1024
+// non-orthogonal 20.9 us a step in 16 x 16, 17.3 in 32 x 16, 17.5 singly; six cases of
+// 256 x 512 64.4, 52.3, 51.8; SRT 42.8, 49.8, 51.0).
 struct TileCost {
     float launch, tile;      // us a step
 };
-constexpr TileCost TILE_COST[2][TILE_SHAPES] = {
-    {{2.5f, 0.85f}, {2.85f, 0.83f}, {2.7f, 1.75f}, {2.9f, 3.0f}},   // FP32
-    {{2.6f, 1.27f}, {3.0f, 1.4f}, {2.85f, 2.8f}, {0.9f, 7.2f}},     // FP64
+constexpr TileCost TILE_COST[2][2][TILE_SHAPES] = {                     // [precision][MRT with free rates, non-orthogonal]
+    {{{2.5f, 0.85f}, {2.85f, 0.83f}, {2.7f, 1.75f}, {2.9f, 3.0f}},      // FP32
+     {{2.8f, 0.85f}, {2.8f, 0.95f}, {2.7f, 2.1f}, {2.7f, 3.45f}}},
+    {{{2.6f, 1.27f}, {3.0f, 1.4f}, {2.85f, 2.8f}, {0.9f, 7.2f}},        // FP64
+     {{2.4f, 1.4f}, {2.75f, 1.55f}, {0.95f, 4.85f}, {0.5f, 8.0f}}},
 };
 constexpr float SINGLE_COST[2] = {7.7f, 11.0f};
 
@@ -1158,6 +1164,8 @@ TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool alone)
         return plan;
     }
     const int64_t cus = cases[0]->cus;
+    const int mode = cases[0]->P64.mode;
+    const bool heavy = mode == COLLIDE_MRT || mode == COLLIDE_NMRT;
     float best = 0.0f;
     for (int shape = 0; shape < TILE_SHAPES; ++shape) {
         int64_t tiles = 0;
@@ -1166,7 +1174,7 @@ TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool alone)
             for (int i = 0; i < n; ++i)
                 tiles += (int64_t)((cases[i]->prm.nz + S::OZ - 1) / S::OZ) * ((cases[i]->prm.nr + S::OR - 1) / S::OR);
         });
-        const TileCost c = TILE_COST[fp64 ? 1 : 0][shape];
+        const TileCost c = TILE_COST[fp64][heavy][shape];
         const float cost = c.launch + c.tile * (float)((tiles + cus - 1) / cus);
         if (shape == 0 || cost <= best) {
             best = cost;

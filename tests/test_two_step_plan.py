@@ -77,3 +77,27 @@ def test_march_of_a_batch_goes_by_its_fullest_xcd(plan_of, precision, resident, 
     tallest = max(g[0] for g in grids)
     best = min(cost(-(-tallest // c)) for c in range(1, tallest // 4 + 1))
     assert cost(p["rows"]) == min(best, cost(4))
+
+
+# us a step as measured on an MI355X: single steps, tiles of 8 x 4, 12 x 8, 16 x 16, 32 x 16
+MEASURED = [
+    ("fp64", NMRT, [(256, 1024, True)], True, (17.3, 46.5, 19.04, 20.67, 17.32)),
+    ("fp64", MRT, [(512, 1024, True)], True, (35.86, 91.37, 35.55, 39.18, 33.45)),
+    ("fp64", NMRT, [(400, 700, True)], True, (25.76, 49.87, 20.25, 23.96, 22.63)),
+    ("fp64", NMRT, [(256, 512, True)] * 4, False, (36.23, 93.63, 37.46, 41.04, 33.96)),
+    ("fp64", MRT, [(256, 512, True)] * 6, False, (52.11, 142.39, 56.01, 64.57, 52.88)),
+    ("fp64", MRT, [(100, 200, True)] * 30, False, (51.42, 117.78, 49.21, 61.1, 57.71)),
+    ("fp64", SRT, [(256, 512, True)] * 6, False, (51.03, 119.46, 51.8, 42.78, 49.79)),
+    ("fp64", UNIT, [(512, 1024, True)], True, (36.14, 76.27, 32.4, 26.29, 31.46)),
+    ("fp32", NMRT, [(512, 1024, True)], True, (20.18, 55.78, 23.1, 19.04, 16.61)),
+]
+
+
+@pytest.mark.parametrize("precision,mode,grids,alone,us", MEASURED)
+def test_tiles_follow_the_measured_times(plan_of, precision, mode, grids, alone, us):
+    """The plan loses no more than the cost model's error (5 %) to single steps,
+    and no more than twice that to the best tile shape."""
+    p = plan_of(precision, grids, alone=alone, mode=mode)
+    assert not p["march"]
+    assert us[p["tile"] + 1] <= 1.05 * us[0]
+    assert us[p["tile"] + 1] <= 1.1 * min(us)
