@@ -1127,7 +1127,9 @@ static void plan_march(const lbm_axi_case *const *cases, int n, bool alone, TwoS
 // 2048 51 against 59.
 // Tiles: the shape whose launch is done first.  A compute unit takes its tiles
 // together or in turn; either way a step takes what a launch and the first
-// latencies do and a share per tile of the fullest unit (TileCost; fitted, within
+// latencies do and a share per tile of the fullest unit (of the XCD that has
+// most: three cases of 42 x 896 FP32 are 252 tiles of 32 x 16, but 33 on the first
+// XCD's 32 units, 9.2 us a step against 7.1 in 16 x 16; TileCost; fitted, within
 // 10 %, to grids of 2 to 690 thousand nodes: 64 x 128 FP32 3.4 us a step in
 // 8 x 4, 3.5 in 12 x 8, 4.1 in 16 x 16; 128 x 512 FP32 4.5 in 16 x 16, 5.4 in
 // 12 x 8, 5.9 in 32 x 16; 300 x 600 FP32 9.7 in 12 x 8, 8.1 in 16 x 16, 8.4 in 32 x 16;
@@ -1163,16 +1165,18 @@ TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool alone)
         plan_march(cases, n, alone, plan);
         return plan;
     }
-    const int64_t cus = cases[0]->cus;
+    const int64_t cus = std::max(1, cases[0]->cus / 8);           // of one XCD
     const int mode = cases[0]->P64.mode;
     const bool heavy = mode == COLLIDE_MRT || mode == COLLIDE_NMRT;
     float best = 0.0f;
     for (int shape = 0; shape < TILE_SHAPES; ++shape) {
-        int64_t tiles = 0;
+        int64_t tiles = 0;                                        // of the fullest XCD: each case's are dealt out evenly
         with_tile_shape(shape, [&](auto t) {
             using S = decltype(t);
-            for (int i = 0; i < n; ++i)
-                tiles += (int64_t)((cases[i]->prm.nz + S::OZ - 1) / S::OZ) * ((cases[i]->prm.nr + S::OR - 1) / S::OR);
+            for (int i = 0; i < n; ++i) {
+                const lbm_axi_params &p = cases[i]->prm;
+                tiles += ((int64_t)((p.nz + S::OZ - 1) / S::OZ) * ((p.nr + S::OR - 1) / S::OR) + 7) / 8;
+            }
         });
         const TileCost c = TILE_COST[fp64][heavy][shape];
         const float cost = c.launch + c.tile * (float)((tiles + cus - 1) / cus);
@@ -1181,7 +1185,7 @@ TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool alone)
             plan.tile = shape;
         }
     }
-    if (alone && best > SINGLE_COST[fp64 ? 1 : 0] && geom_for(cases[0], 8).tiles <= cus) plan.tile = -1;
+    if (alone && best > SINGLE_COST[fp64 ? 1 : 0] && geom_for(cases[0], 8).tiles <= cases[0]->cus) plan.tile = -1;
     return plan;
 }
 
