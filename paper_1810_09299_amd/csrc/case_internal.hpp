@@ -24,7 +24,11 @@ struct TwoStepPlan {
     bool march;            // strips marching up the rows (axi_pair.hpp), else tiles (axi_tile.hpp)
     int waves, rows;       // march: wavefronts of a workgroup, rows of a run
     int tile;              // tiles: the shape (with_tile_shape); -1: steps go singly
+    float tiles_us;        // tiles: what a step is estimated to take, and
+    float single_us;       // what a single one is (infinite where it is no choice)
 };
+// single steps are chosen within the estimates' error of 4 %
+inline bool singly_ahead(float single_us, float tiles_us) { return single_us < 1.04f * tiles_us; }
 
 } // namespace axi
 
@@ -61,7 +65,8 @@ int64_t plane_elems(int nr, int nz);
 // how many strips `waves` wavefronts cut nz columns into (axi_pair.hpp)
 int pair_strips(int nz, int z_periodic, int waves);
 // two steps per launch for the n cases of one launch: the plan that suits them
-// (alone: the one case's own launch, which may also step singly; else a batch's)
+// (alone: the one case's own launch, which then may also be to step singly;
+// else a batch's, which decides for all its launches)
 TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool alone);
 // whether what is enqueued on the stream now is being recorded into a graph
 bool recording(hipStream_t stream);

@@ -1134,11 +1134,6 @@ static void plan_march(const lbm_axi_case *const *cases, int n, bool alone, TwoS
 // 8 x 4, 3.5 in 12 x 8, 4.1 in 16 x 16; 128 x 512 FP32 4.5 in 16 x 16, 5.4 in
 // 12 x 8, 5.9 in 32 x 16; 300 x 600 FP32 9.7 in 12 x 8, 8.1 in 16 x 16, 8.4 in 32 x 16;
 // 128 x 2048 10.5 and 9.3 in the last two, FP64 15.9 and 16.9).
-// Single steps took 5.2 (64 x 128, FP32, the default tile), 7.8 (60 x 286,
-// FP64), 11.1 (128 x 2048, FP32).  Only where they, in 64 x 8, need one tile per
-// unit and the smaller tiles of two steps, by their ragged edges, more, do they
-// stay ahead (69 x 1717 FP32: 7.7 against 8.5; 133 x 920 FP64, SRT: 11.5 against
-// 13.2), so a case steps singly there.
 // The general and the non-orthogonal MRT hold more registers: in FP64 a unit
 // takes one 16 x 16 tile of theirs at a time, two of the other forms' (256 x 1024
 // non-orthogonal 20.9 us a step in 16 x 16, 17.3 in 32 x 16, 17.5 singly; six cases of
@@ -1147,16 +1142,48 @@ struct TileCost {
     float launch, tile;      // us a step
 };
 constexpr TileCost TILE_COST[2][2][TILE_SHAPES] = {                     // [precision][MRT with free rates, non-orthogonal]
-    {{{2.5f, 0.85f}, {2.85f, 0.83f}, {2.7f, 1.75f}, {2.9f, 3.0f}},      // FP32
+    {{{2.6f, 0.75f}, {2.75f, 0.82f}, {2.65f, 1.8f}, {2.85f, 3.05f}},    // FP32
      {{2.8f, 0.85f}, {2.8f, 0.95f}, {2.7f, 2.1f}, {2.7f, 3.45f}}},
-    {{{2.6f, 1.27f}, {3.0f, 1.4f}, {2.85f, 2.8f}, {0.9f, 7.2f}},        // FP64
+    {{{2.5f, 1.2f}, {2.6f, 1.45f}, {2.55f, 3.1f}, {0.65f, 7.5f}},       // FP64
      {{2.4f, 1.4f}, {2.75f, 1.55f}, {0.95f, 4.85f}, {0.5f, 8.0f}}},
 };
-constexpr float SINGLE_COST[2] = {7.7f, 11.0f};
+// Single steps take more (5.2 us a step of 64 x 128 FP32, 7.8 of 60 x 286 FP64,
+// 11.1 of 128 x 2048 FP32), but while each of their 64 x 8 tiles has a unit to
+// itself, and the smaller tiles of two steps, by their ragged edges, need a
+// round more, they stay ahead: 69 x 1717 FP32 7.7 against 8.2 in the best shape,
+// 200 x 640 6.3 against 7.5, FP64 9.7 against 11.1, 133 x 920 9.7 against 11.2.
+// Then a step takes a launch and a share per tile by how its rows lie in memory:
+// whole 64-byte lines, half ones, neither (fitted likewise, within 5 %; 256 tiles
+// FP32 6.2 us in rows of 512 nodes, 7.3 of 504, 8.0 of 511).  Batches of more
+// than eight cases were never ahead singly (14 of 30 x 208 FP32 8.7 against 7.3).
+struct SingleCost {
+    float launch, line, half, ragged;
+};
+constexpr SingleCost SINGLE_COST[2][2] = {
+    {{4.6f, 0.0068f, 0.0103f, 0.0125f}, {4.9f, 0.0065f, 0.0101f, 0.0119f}},
+    {{5.9f, 0.0148f, 0.0215f, 0.0244f}, {6.3f, 0.0135f, 0.0209f, 0.024f}},
+};
+constexpr int SINGLY_CASES = 8;
+
+// us a step of single steps (64 x 8 tiles in 16 bands a case, the default), or
+// infinity where two steps are ahead anyway
+static float single_us(const lbm_axi_case *const *cases, int n, const SingleCost &c)
+{
+    const int es = cases[0]->prm.precision == LBM_AXI_FP64 ? 8 : 4, cus = std::max(1, cases[0]->cus / 8);
+    int fullest = 0;                                              // tiles on the first XCD
+    float us = c.launch;
+    for (int i = 0; i < n; ++i) {
+        const lbm_axi_params &p = cases[i]->prm;
+        const int tiles = geom_for(cases[i], 8).tiles, row = p.nz % 64 * es;
+        fullest += n == 1 ? (tiles + 7) / 8 : tiles / 16 * 2 + (tiles % 16 > 0) + (tiles % 16 > 8);
+        us += (float)tiles * (row % 64 == 0 ? c.line : (row % 32 == 0 ? c.half : c.ragged));
+    }
+    return n > SINGLY_CASES || fullest > cus ? INFINITY : us;
+}
 
 TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool alone)
 {
-    TwoStepPlan plan{false, 1, 4, 0};
+    TwoStepPlan plan{false, 1, 4, 0, 0.0f, INFINITY};
     const bool fp64 = cases[0]->prm.precision == LBM_AXI_FP64;
     int64_t nodes = 0;
     for (int i = 0; i < n; ++i) nodes += (int64_t)cases[i]->prm.nr * cases[i]->prm.nz;
@@ -1168,7 +1195,6 @@ TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool alone)
     const int64_t cus = std::max(1, cases[0]->cus / 8);           // of one XCD
     const int mode = cases[0]->P64.mode;
     const bool heavy = mode == COLLIDE_MRT || mode == COLLIDE_NMRT;
-    float best = 0.0f;
     for (int shape = 0; shape < TILE_SHAPES; ++shape) {
         int64_t tiles = 0;                                        // of the fullest XCD: each case's are dealt out evenly
         with_tile_shape(shape, [&](auto t) {
@@ -1179,13 +1205,14 @@ TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool alone)
             }
         });
         const TileCost c = TILE_COST[fp64][heavy][shape];
-        const float cost = c.launch + c.tile * (float)((tiles + cus - 1) / cus);
-        if (shape == 0 || cost <= best) {
-            best = cost;
+        const float us = c.launch + c.tile * (float)((tiles + cus - 1) / cus);
+        if (shape == 0 || us <= plan.tiles_us) {
+            plan.tiles_us = us;
             plan.tile = shape;
         }
     }
-    if (alone && best > SINGLE_COST[fp64 ? 1 : 0] && geom_for(cases[0], 8).tiles <= cases[0]->cus) plan.tile = -1;
+    plan.single_us = single_us(cases, n, SINGLE_COST[fp64][heavy]);
+    if (alone && singly_ahead(plan.single_us, plan.tiles_us)) plan.tile = -1;
     return plan;
 }
 

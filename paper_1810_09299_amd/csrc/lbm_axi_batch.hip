@@ -473,6 +473,7 @@ void build_pairs(lbm_axi_batch *b, const std::vector<int> &order)
     b->pair_work.clear();
     for (int q = 0; q <= NMODE; ++q) b->pair_start[q] = 0;
     if (b->precision == LBM_AXI_FP16D) return;
+    float tiles_us = 0.0f, single_us = 0.0f;         // of a step, all forms
     for (size_t first = 0, end; first < order.size(); first = end) {
         const int mode = b->cases[order[first]]->P64.mode;
         std::vector<const lbm_axi_case *> form;
@@ -480,6 +481,8 @@ void build_pairs(lbm_axi_batch *b, const std::vector<int> &order)
             form.push_back(b->cases[order[end]]);
         const TwoStepPlan plan = two_step_plan(form.data(), (int)form.size(), false);
         b->plan[mode] = plan;
+        tiles_us += plan.tiles_us;
+        single_us += plan.single_us;
         std::vector<WorkItem> queue[8];
         int next = 0;
         for (size_t i = 0; i < form.size(); ++i) {
@@ -504,6 +507,9 @@ void build_pairs(lbm_axi_batch *b, const std::vector<int> &order)
             for (const auto &x : queue) b->pair_work.push_back(l < x.size() ? x[l] : WorkItem{-1, 0, 0, 0});
         for (int q = mode + 1; q <= NMODE; ++q) b->pair_start[q] = (int)b->pair_work.size();
     }
+    // few cases may be ahead singly (every launch flips the phase of all: all
+    // forms go one way)
+    if (singly_ahead(single_us, tiles_us)) b->pair_work.clear();
     // both lists share the reserved area
     if (b->work.size() + b->pair_work.size() > (size_t)MAX_WORK) b->pair_work.clear();
 }
@@ -849,7 +855,7 @@ int lbm_axi_batch_create(void *dev_pool, size_t pool_bytes, int32_t max_cases, i
     b->dirty = true;
     for (int q = 0; q <= NCLASS; ++q) b->mode_start[q] = 0;
     for (int q = 0; q <= NMODE; ++q) b->pair_start[q] = 0;
-    for (TwoStepPlan &w : b->plan) w = TwoStepPlan{false, 1, 4, 0};
+    for (TwoStepPlan &w : b->plan) w = TwoStepPlan{false, 1, 4, 0, 0.0f, 0.0f};
     b->launches = 0;
     *out = b;
     return LBM_AXI_OK;

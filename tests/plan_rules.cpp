@@ -20,7 +20,9 @@ int main()
             ptrs.push_back(&c);
         }
         const axi::TwoStepPlan p = axi::two_step_plan(ptrs.data(), n, alone != 0);
-        printf("%d %d %d %d\n", (int)p.march, p.waves, p.rows, p.tile);
+        // tile -1: singly (a batch of one collision form decides as build_pairs does)
+        const bool singly = !p.march && (p.tile < 0 || (!alone && axi::singly_ahead(p.single_us, p.tiles_us)));
+        printf("%d %d %d %d\n", (int)p.march, p.waves, p.rows, singly ? -1 : p.tile);
     }
     return 0;
 }

@@ -98,6 +98,16 @@ MEASURED = [
     # 64 x 8 tiles of single steps fit one to a unit where the smaller ones do not
     ("fp32", UNIT, [(200, 640, True)], True, (6.3, 14.47, 7.51, 7.78, 8.13)),
     ("fp64", UNIT, [(200, 640, True)], True, (9.72, 21.14, 11.14, 11.5, 13.69)),
+    ("fp64", SRT, [(69, 1717, True)], True, (11.74, 23.28, 11.82, 12.13, 15.47)),
+    ("fp32", NMRT, [(69, 1717, True)], True, (7.83, 16.97, 8.89, 9.48, 9.68)),
+    ("fp32", NMRT, [(166, 448, True)], True, (5.78, 11.08, 6.43, 6.68, 6.22)),
+    ("fp32", UNIT, [(63, 2047, True)], True, (7.98, 15.92, 8.17, 6.64, 6.26)),
+    # the same in a batch of few cases
+    ("fp32", UNIT, [(69, 1717, True)], False, (8.04, 15.67, 8.46, 8.84, 8.96)),
+    ("fp64", UNIT, [(133, 920, True)], False, (10.54, 22.96, 11.99, 11.82, 14.58)),
+    ("fp32", NMRT, [(125, 784, True)], False, (6.36, 14.4, 7.85, 7.31, 6.7)),
+    ("fp32", UNIT, [(382, 224, True)], False, (5.81, 11.01, 6.1, 6.05, 6.05)),
+    ("fp32", UNIT, [(30, 208, True)] * 14, False, (8.66, 13.48, 7.3, 7.93, 7.37)),
 ]
 
 
