@@ -16,8 +16,8 @@ timed runs replay are captured before the timed region.  Prints one JSON line:
   roofline      the batched step kernel against MI355X's 8 TB/s HBM:
                 algorithmic bytes per launch (the state of every node read once
                 and written once) over the mean launch duration, from HIP events
-                on the batch's stream around the timed region;
-                steps_per_launch steps each
+                on the batch's stream around the timed region over its launches;
+                steps_per_launch steps each on average
   variants      the batch in the other storage precisions; the batch with the
                 SRT and non-orthogonal MRT collision forms in every precision;
                 FP16-deviation storage with stochastic g rounding; single case
@@ -55,8 +55,9 @@ HBM_PEAK_GBS = 8000.0
 # exact mass and so moves 100 B; the algorithmic count is the method's 96 B.)
 BYTES_PER_LU = {"fp64": 18 * 8 * 2 + 3 * 8 * 2, "fp32": 18 * 4 * 2 + 3 * 4 * 2,
                 "fp16": 18 * 2 * 2 + 3 * 4 * 2}
-# time steps that one launch advances
-STEPS_PER_LAUNCH = {"fp64": 2, "fp32": 2, "fp16": 1}
+# FP64 and FP32 steps go in pairs, one launch each (the cases here are never
+# ahead singly); from this many nodes on the launch marches, below it goes in tiles
+MARCH_NODES = {"fp64": 800_000, "fp32": 1_200_000}
 MOVED_BYTES_PER_LU = dict(BYTES_PER_LU, fp16=(4 + 8 * 2 + 9 * 2) * 2 + 3 * 4 * 2)
 WORKLOAD = "oscillating_droplet"
 CHUNK = 100
@@ -93,18 +94,36 @@ def step_plan(steps: int, chunk: int = CHUNK) -> list:
     return plan
 
 
-def measured_traffic(precision: str, config, cases: int) -> float | None:
+def launches(precision: str, runs) -> int:
+    """Kernel launches that runs of these many steps take: one per two steps in
+    FP64 and FP32 and one for an odd step left at a run's end."""
+    return sum(m if precision == "fp16" else m // 2 + m % 2 for m in runs)
+
+
+def kernel_name(precision: str, nodes: int, runs) -> str:
+    """The batch's kernel that does most of the runs' launches."""
+    if precision == "fp16":
+        return "batch_step_kernel_h"
+    if max(runs) < 2:
+        return "batch_step_kernel"
+    return "batch_pair_kernel" if nodes >= MARCH_NODES[precision] else "batch_tile_kernel"
+
+
+def measured_traffic(precision: str, config, cases: int, runs) -> float | None:
     """HBM bytes per launch from the committed rocprofv3 counter summary, if it
     was taken on the current kernel source with the same number of cases and
-    launch configuration (tile rows, persistent, schedule, bands; a launch of
-    two steps takes none of these); else None."""
+    launch configuration (tile rows, persistent, schedule, bands; launches of
+    two steps take none of these); else None, and where launches of one and two
+    steps are mixed."""
     path = os.path.join(ROOT, "profiles", "batch_step_kernel_oscillating_droplet_traffic.json")
     if not os.path.exists(path):
         return None
     with open(path) as fh:
         d = json.load(fh)
     key = f"{cases}/{config['tile_rows']}/{config['persistent']}/{config['schedule']}/{config['bands']}"
-    if STEPS_PER_LAUNCH[precision] == 2:
+    if precision != "fp16":
+        if any(m % 2 for m in runs):
+            return None
         key = f"{cases}/two_steps"
     rec = d.get(precision, {}).get(key)
     if not rec or rec.get("source_hash") != kernel_source_hash():
@@ -166,13 +185,15 @@ def run_batch(specs, precision, steps, warmup, config=None):
     finite = all(d[2] == 0 for d in diags)
     b.close()
     nodes = sum(s.nr * s.nz for s in specs)
-    step_ms, kernel_ms = ev_ms / k, ev_ms / k * STEPS_PER_LAUNCH[precision]
+    count = launches(precision, timed)
+    step_ms, kernel_ms = ev_ms / k, ev_ms / count
     note(f"batch {len(specs)} x {specs[0].nr}x{specs[0].nz} {precision} {specs[0].collision} config {config}: "
          f"{step_ms * 1e3:.2f} us per step, {nodes * k / wall / 1e6:.0f} MLUPS")
     bytes_launch = nodes * BYTES_PER_LU[precision]
     return {"mlups": nodes * k / wall / 1e6, "ms_per_step": wall / k * 1e3, "kernel_ms": kernel_ms, "step_ms": step_ms,
             "achieved_GBs": bytes_launch / (kernel_ms * 1e-3) / 1e9, "bytes_per_launch": bytes_launch,
-            "steps": k, "config": {"tile_rows": config[0], "persistent": config[1], "schedule": config[2],
+            "steps": k, "launches": count, "kernel": kernel_name(precision, nodes, timed), "runs": timed,
+            "steps_per_launch": k / count, "config": {"tile_rows": config[0], "persistent": config[1], "schedule": config[2],
                                    "bands": config[3]},
             "finite": finite, "t_final": diags[0][1]["t"]}
 
@@ -220,7 +241,7 @@ def run_single(spec, precision, steps, warmup):
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     nodes = spec.nr * spec.nz
-    kernel_ms = start.elapsed_time(end) / steps * STEPS_PER_LAUNCH[precision]
+    kernel_ms = start.elapsed_time(end) / launches(precision, [steps])
     return {"mlups": nodes * steps / wall / 1e6, "kernel_ms": kernel_ms,
             "achieved_GBs": nodes * BYTES_PER_LU[precision] / (kernel_ms * 1e-3) / 1e9, "tile_rows": tile}
 
@@ -367,9 +388,9 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(main_res["achieved_GBs"], 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(main_res["achieved_GBs"] / HBM_PEAK_GBS, 4),
                      "traffic": (None if stochastic else
-                                 measured_traffic(args.precision, main_res["config"], args.cases)),
-                     "kernel": "batch_step_kernel_h" if args.precision == "fp16" else "batch_pair_kernel",
-                     "steps_per_launch": STEPS_PER_LAUNCH[args.precision],
+                                 measured_traffic(args.precision, main_res["config"], args.cases, main_res["runs"])),
+                     "kernel": main_res["kernel"],
+                     "steps_per_launch": round(main_res["steps_per_launch"], 4),
                      "kernel_ms_mean": round(main_res["kernel_ms"], 5),
                      "bytes_per_launch": main_res["bytes_per_launch"],
                      "copy_GBs": round(copy_gbs, 1), "frac_of_copy": round(main_res["achieved_GBs"] / copy_gbs, 4)},
@@ -386,8 +407,8 @@ def main():
             line["variants"][f"batch_{other}"] = {
                 "mlups": round(ob["mlups"], 1), "frac": round(ob["achieved_GBs"] / HBM_PEAK_GBS, 4),
                 "frac_of_copy": round(ob["achieved_GBs"] / copy_gbs, 4),
-                "kernel_ms_mean": round(ob["kernel_ms"], 5), "bytes_per_lu": BYTES_PER_LU[other] / STEPS_PER_LAUNCH[other],
-                "moved_bytes_per_lu": MOVED_BYTES_PER_LU[other] / STEPS_PER_LAUNCH[other], **ob["config"]}
+                "kernel_ms_mean": round(ob["kernel_ms"], 5), "bytes_per_lu": round(BYTES_PER_LU[other] / ob["steps_per_launch"], 3),
+                "moved_bytes_per_lu": round(MOVED_BYTES_PER_LU[other] / ob["steps_per_launch"], 3), **ob["config"]}
         # the same batch at a quarter of the cases (411 MB in FP32), launch
         # configuration of the full batch
         if args.cases >= 32:
