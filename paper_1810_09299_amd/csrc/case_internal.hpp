@@ -68,6 +68,8 @@ int pair_strips(int nz, int z_periodic, int waves);
 // (alone: the one case's own launch, which then may also be to step singly;
 // else a batch's, which decides for all its launches)
 TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool alone);
+// rows of the single step's tile where the caller names none
+int default_tile(const lbm_axi_case *c);
 // whether what is enqueued on the stream now is being recorded into a graph
 bool recording(hipStream_t stream);
 // how many of n steps go in pairs.  A graph holds the addresses of the buffer

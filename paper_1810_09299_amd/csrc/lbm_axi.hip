@@ -1220,11 +1220,17 @@ TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool alone)
 // FP16-deviation storage, 4 while every such tile has a compute unit to itself
 // (then it is the time of one tile that counts: 150 x 300 5.6 us a step against
 // 6.1, 128 x 256 5.4 against 5.7; beyond, the larger share of ring costs more:
-// 256 x 512 6.3 against 6.0).  FP64 and FP32 step singly only for an odd step
-// out or in a recording: 64 x 128 FP32 measured the same either way.
-static int default_tile(const lbm_axi_case *c)
+// 256 x 512 6.3 against 6.0).  Not where the last tile column holds a few
+// columns only, nearly all of it ghost cells, of which a thread of the smaller
+// tile takes two (200 x 65 8.2 us against 7.6, 60 x 321 with walls 8.3 against
+// 7.0), nor for the non-orthogonal MRT, whose registers spill (60 x 344 6.5
+// against 6.2, 200 x 48 6.3 against 6.1).  FP64 and FP32: 64 x 128 FP32 measured
+// the same either way.
+int default_tile(const lbm_axi_case *c)
 {
-    if (c->prm.precision != LBM_AXI_FP16D) return 8;
+    if (c->prm.precision != LBM_AXI_FP16D || c->P64.mode == COLLIDE_NMRT) return 8;
+    const int last = c->prm.nz % TZ;
+    if (last > 0 && last <= 10) return 8;
     const int64_t tiles = (int64_t)((c->prm.nz + TZ - 1) / TZ) * ((c->prm.nr + 3) / 4);
     return tiles <= c->cus ? 4 : 8;
 }
@@ -1403,7 +1409,6 @@ int lbm_axi_init(const lbm_axi_params *params, void *dev_state, size_t dev_bytes
     c->recorded = false;
     c->cus = 256;
     (void)hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev);
-    c->tile_r = default_tile(c);
     c->esize = L.esize;
     for (int b = 0; b < 2; ++b)
         for (int q = 0; q < 2; ++q)
@@ -1416,6 +1421,7 @@ int lbm_axi_init(const lbm_axi_params *params, void *dev_state, size_t dev_bytes
     c->P64 = make_phys<double>(params);
     c->P32 = make_phys<float>(params);
     c->codec = make_codec(params);
+    c->tile_r = default_tile(c);
     c->geom = geom_for(c, c->tile_r);
     c->two = two_step_plan(&c, 1, true);
 

@@ -1,4 +1,4 @@
-"""How launches of two steps are planned (two_step_plan), without a GPU: a small
+"""How launches are planned (two_step_plan, default_tile), without a GPU: a small
 program linked to the library prints the plan of given grids."""
 import os
 import shutil
@@ -24,11 +24,11 @@ def plan_of(tmp_path_factory):
                    check=True, capture_output=True, text=True, timeout=300)
 
     def plan(precision, grids, alone=False, mode=UNIT):
-        line = f"{int(alone)} {int(precision == 'fp64')} {mode} {len(grids)} "
+        line = f"{int(alone)} {abi.PRECISIONS[precision]} {mode} {len(grids)} "
         line += " ".join(f"{nr} {nz} {int(zper)}" for nr, nz, zper in grids)
         r = subprocess.run([exe], input=line, check=True, capture_output=True, text=True, timeout=60)
-        march, waves, rows, tile = map(int, r.stdout.split())
-        return {"march": bool(march), "waves": waves, "rows": rows, "tile": tile}
+        march, waves, rows, tile, single_rows = map(int, r.stdout.split())
+        return {"march": bool(march), "waves": waves, "rows": rows, "tile": tile, "single_rows": single_rows}
 
     return plan
 
@@ -119,3 +119,16 @@ def test_tiles_follow_the_measured_times(plan_of, precision, mode, grids, alone,
     assert not p["march"]
     assert us[p["tile"] + 1] <= 1.05 * us[0]
     assert us[p["tile"] + 1] <= 1.1 * min(us)
+
+
+# FP16-deviation storage, us a step as measured in 64 x 4 and 64 x 8 tiles
+HALF = [(UNIT, 150, 300, True, 5.6, 6.1), (UNIT, 200, 65, True, 8.2, 7.6), (UNIT, 200, 72, False, 8.2, 7.5),
+        (SRT, 60, 321, False, 8.4, 7.3), (MRT, 200, 68, True, 9.3, 8.2), (MRT, 160, 328, False, 8.9, 7.8),
+        (NMRT, 60, 344, False, 6.5, 6.2), (NMRT, 200, 48, True, 6.3, 6.1), (MRT, 160, 380, True, 6.0, 6.4),
+        (UNIT, 256, 512, True, 6.3, 6.0)]
+
+
+@pytest.mark.parametrize("mode,nr,nz,zper,four,eight", HALF)
+def test_fp16_default_tile_follows_the_measured_times(plan_of, mode, nr, nz, zper, four, eight):
+    rows = plan_of("fp16", [(nr, nz, zper)], alone=True, mode=mode)["single_rows"]
+    assert rows == (4 if four < eight else 8)
