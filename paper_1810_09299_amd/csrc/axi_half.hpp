@@ -620,7 +620,12 @@ __device__ __forceinline__ void tile_step_h(const Geom &g, const Phys<float> &P,
     read_stencil<float, TZ>(tile, tx, ty, st);
     const float r = (float)j + 0.5f, ir = inv_radius<float>(j);
     Macro<float> m;
-    macro_state<MOMENTS ? FORM_OF_P : MODE>(P, r, ir, st, gv, uzp, urp, m);
+    // the form is compiled into the macroscopic state for the two MRT kernels
+    // whose registers spill (32 cases of 256 x 512: general 102.9 -> 95.4 us a step,
+    // non-orthogonal 97.6 -> 93.2); the others are faster with it read from P
+    // (64 cases, unit rates 176.7 -> 175.6; one case of 69 x 66 7.8 -> 7.4)
+    constexpr bool COMPILED = !MOMENTS && (MODE == COLLIDE_MRT || MODE == COLLIDE_NMRT);
+    macro_state<COMPILED ? MODE : FORM_OF_P>(P, r, ir, st, gv, uzp, urp, m);
     if constexpr (MOMENTS) {
         const int64_t n = (int64_t)j * g.nz + k;
         F.phi[n] = (double)m.phi;
