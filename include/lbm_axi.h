@@ -221,10 +221,12 @@ int lbm_axi_destroy(lbm_axi_case *c);
 
 /* ------------------------------------------------------------------ batches
  * Many independent cases -- any grid sizes, parameters and step counts, one
- * precision -- advanced together: every time step, or every two of large FP64
- * and FP32 batches, is one kernel launch over all running cases (the same per-node arithmetic as a case run alone, so
- * their populations are bit-identical).  Runs of steps over an unchanged set
- * of running cases are captured once in a hipGraph and replayed.
+ * precision -- advanced together: every two time steps in FP64 and FP32 storage
+ * (every one where that is ahead), every step in FP16-deviation storage, is one
+ * kernel launch per collision form over the running cases of that form (the
+ * same per-node arithmetic as a case run alone, so their populations are
+ * bit-identical).  Runs of steps over an unchanged set of running cases are
+ * captured once in a hipGraph and replayed.
  *
  * Memory: the caller hands over one device pool (256-byte aligned).  Its
  * first lbm_axi_batch_reserved_bytes() bytes hold the case table, the work
@@ -256,8 +258,8 @@ int lbm_axi_batch_admit(lbm_axi_batch *b, const lbm_axi_params *params, const do
                         int64_t nsteps, int32_t *slot);
 
 /* Advances every running case by min(chunk_steps, its remaining steps):
- * one launch per step, or per two steps in FP64 and FP32 storage; cases that
- * reach their step count stop there.
+ * one launch per step, or per two steps in FP64 and FP32 storage (per collision
+ * form); cases that reach their step count stop there.
  * Asynchronous: a change in the set of running cases re-uploads the case
  * table and work list through a pinned staging buffer, ordered on the stream
  * after the steps already enqueued.  A run of chunk_steps steps over an
@@ -289,7 +291,9 @@ int lbm_axi_batch_get_state(lbm_axi_batch *b, int32_t slot, double *f, double *g
  * work that last touched it has completed. */
 int lbm_axi_batch_release(lbm_axi_batch *b, int32_t slot);
 
-/* Launch configuration (results do not depend on it): tile_r rows per tile in
+/* Launch configuration (results do not depend on it) of launches of one step;
+ * launches of two steps, whose shape goes by the sizes, take none of it but the
+ * case order.  tile_r rows per tile in
  * {2, 4, 8, 16} (0: 8); persistent 0 = one workgroup per tile, 1 = a
  * resident grid striding over the tiles; schedule in 0..3: bit 0 set = largest
  * case first, else cases in slot order; bands in {8, 16, 32} (0: 16) =
@@ -302,7 +306,8 @@ int lbm_axi_batch_set_config(lbm_axi_batch *b, int32_t tile_r, int32_t persisten
                              int32_t bands);
 
 /* Occupancy of the batch: slots in use, running cases, free pool bytes, and
- * the number of time steps launched so far.  Any pointer may be NULL. */
+ * the number of time steps launched so far (a launch of two counts as two).
+ * Any pointer may be NULL. */
 int lbm_axi_batch_info(const lbm_axi_batch *b, int32_t *n_used, int32_t *n_running, size_t *free_bytes,
                        int64_t *launches);
 

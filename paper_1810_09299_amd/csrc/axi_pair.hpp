@@ -27,13 +27,13 @@
 // old values.)
 //
 // Measured, us per step, one step per launch -> two (best tile each):
-//   64 cases 256 x 512 FP32      249.5 -> 155 (1.41 GB read and written, 5.6 TB/s
-//                                -> 1.7 GB per two steps at 4.9)
-//   32 cases 256 x 512 FP64      250.6 -> 166
-//   one case 512 x 2048 FP32      37.5 -> 30
-// What bounds it now: vector instructions issue 0.74 of the time (FP32), at a
-// clock that power holds at 2.0 of 2.4 GHz, beside 0.88 of the bandwidth that
-// the single steps reach; FP64 runs one wavefront per SIMD (LDS, registers).
+//   64 cases 256 x 512 FP32      249.5 -> 154.5 (1.48 GB moved per step at 6.0
+//                                TB/s -> per two steps at 4.8)
+//   32 cases 256 x 512 FP64      250.6 -> 165.5
+//   one case 700 x 2000 FP32      50.7 -> 31.5
+// What bounds it now: vector instructions issue two thirds of the time (FP32),
+// at a clock that power holds at 2.0 to 2.1 of 2.4 GHz, beside the ~40 memory
+// streams; FP64 runs one wavefront per SIMD (LDS, registers).
 #pragma once
 
 #include "axi_device.hpp"
@@ -42,8 +42,9 @@ namespace axi {
 
 constexpr int PAIR_HALO = 5;         // lanes lost on each side of a strip
 // cache policy of the stores: the default, so that L2 puts the halves of a line
-// that two strips write together (64 cases FP32: nt 187 us a step against 172,
-// nt sc1 worse)
+// that two strips write together (nt sc1: 40 cases of 200 x 500 FP32 143 us a
+// step against 85.6, 32 of 256 x 512 FP64 208 against 165; with one strip to a
+// case, 64 of 256 x 512 FP32, 154.8 against 154.5)
 constexpr int PAIR_STORE = 0;
 // most wavefronts of a workgroup (FP32 by LDS; FP64: four measured slower than two)
 template <typename R>

@@ -15,8 +15,8 @@
 //
 // Two steps of an FP64 or FP32 case are one launch of pair_kernel (large cases,
 // axi_pair.hpp) or tile_kernel (small ones, axi_tile.hpp).  A step on its own --
-// the odd one out, in a recording, FP16-deviation storage -- is one
-// launch of step_kernel: every workgroup owns a 64 x TR tile,
+// the odd one out, in a recording, where single steps are ahead, FP16-deviation
+// storage -- is one launch of step_kernel: every workgroup owns a 64 x TR tile,
 // pulls the f populations of its tile plus a 2-cell ring (the ring's extra
 // reads hit L2), forms phi in LDS, and then finishes its own nodes: stencil,
 // pressure, velocity, both collisions, store.  No grid-wide synchronisation.
@@ -1122,18 +1122,18 @@ static void plan_march(const lbm_axi_case *const *cases, int n, bool alone, TwoS
 }
 
 // Marching takes too long to start for what fits the caches: one FP32 case of
-// 512 x 1024 21.5 us a step against 15.2 in tiles, of 512 x 2048 30 against 28,
-// 16 cases of 256 x 512 46 against 57; FP64, 512 x 1024 30 against 26, 512 x
-// 2048 51 against 59.
+// 512 x 1024 21.4 us a step against 15.3 in tiles, of 512 x 2048 30 against 27,
+// of 700 x 2000 31.5 against 34.8, 16 cases of 256 x 512 47 against 60; FP64,
+// 512 x 1024 30 against 26, 600 x 1500 43 against 50.
 // Tiles: the shape whose launch is done first.  A compute unit takes its tiles
 // together or in turn; either way a step takes what a launch and the first
 // latencies do and a share per tile of the fullest unit (of the XCD that has
 // most: three cases of 42 x 896 FP32 are 252 tiles of 32 x 16, but 33 on the first
-// XCD's 32 units, 9.2 us a step against 7.1 in 16 x 16; TileCost; fitted, within
-// 10 %, to grids of 2 to 690 thousand nodes: 64 x 128 FP32 3.4 us a step in
-// 8 x 4, 3.5 in 12 x 8, 4.1 in 16 x 16; 128 x 512 FP32 4.5 in 16 x 16, 5.4 in
-// 12 x 8, 5.9 in 32 x 16; 300 x 600 FP32 9.7 in 12 x 8, 8.1 in 16 x 16, 8.4 in 32 x 16;
-// 128 x 2048 10.5 and 9.3 in the last two, FP64 15.9 and 16.9).
+// XCD's 32 units, 9.2 us a step against 7.1 in 16 x 16; TileCost; fitted, 5 % rms,
+// to 550 cases and batches of 20 to 1200 thousand nodes: 128 x 512 FP32 4.4 in
+// 16 x 16, 5.1 in 12 x 8, 5.8 in 32 x 16; 300 x 600 FP32 9.4 in 12 x 8, 8.0 in
+// 16 x 16, 8.4 in 32 x 16; 256 x 1024 10.0 and 8.9 in the last two, FP64 15.0 and
+// 16.3).
 // The general and the non-orthogonal MRT hold more registers: in FP64 a unit
 // takes one 16 x 16 tile of theirs at a time, two of the other forms' (256 x 1024
 // non-orthogonal 20.9 us a step in 16 x 16, 17.3 in 32 x 16, 17.5 singly; six cases of

@@ -7,10 +7,11 @@
 // decided by HBM footprint.
 //
 // FP64 and FP32 batches advance two steps per launch where both are wanted
-// (build_pairs: marching strips or tiles, by size); the odd step out, and every
-// step in FP16-deviation storage, is a launch of batch_step_kernel(_h) over the
-// work list (one per collision form present, see COLLIDE_*): item w = (slot,
-// tile) runs the same tile body as the single-case kernel.  Either way every
+// (build_pairs: marching strips or tiles, by size); the odd step out, every step
+// in FP16-deviation storage, of few cases that are ahead singly, or recorded by
+// the caller, is a launch of batch_step_kernel(_h) over the work list (one per
+// collision form present, see COLLIDE_*): item w = (slot, tile) runs the same
+// tile body as the single-case kernel.  Either way every
 // case's populations are bit-identical to running it alone.  Runs of steps with
 // an unchanged set of running cases replay a captured hipGraph.
 // The host keeps each case's step count and ping-pong parity; a case stops
@@ -462,12 +463,14 @@ bool ramping_at(const lbm_axi_case *c, int64_t t)
 }
 
 // The work lists of the two-step launches for the running cases (`order`:
-// grouped by collision form), or none (FP16-deviation storage: a second step in
-// the launch pays its encoding and decoding again, on the halo too; in tiles
-// 150 x 300 took 6.4 us a step against 5.6 singly, 256 x 512 8.9 against 5.9).  Marching, the strips of one run of rows
-// go to one XCD (they share the lines at their edges; 64 cases of 256 x 512 in
-// FP32: 185 -> 167 us a step), run after run round the XCDs; tiles go as eight
-// runs of neighbours.  Position p runs on XCD p % 8.
+// grouped by collision form), or none: of few cases that are ahead singly, and
+// in FP16-deviation storage (a second step in the launch pays its encoding and
+// decoding again, on the halo too; in tiles 150 x 300 took 6.4 us a step against
+// 5.6 singly, 256 x 512 8.9 against 5.9).  Marching, the strips of one run of
+// rows go to one XCD (they share the lines at their edges; dealt singly, 20
+// cases of 200 x 500 FP64 took 101.2 us a step against 100.1, 64 of 256 x 448
+// FP32 159.6 against 158.7), run after run round the XCDs; tiles go as eight runs
+// of neighbours.  Position p runs on XCD p % 8.
 void build_pairs(lbm_axi_batch *b, const std::vector<int> &order)
 {
     b->pair_work.clear();
