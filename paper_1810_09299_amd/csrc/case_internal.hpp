@@ -24,11 +24,11 @@ struct TwoStepPlan {
     bool march;            // strips marching up the rows (axi_pair.hpp), else tiles (axi_tile.hpp)
     int waves, rows;       // march: wavefronts of a workgroup, rows of a run
     int tile;              // tiles: the shape (with_tile_shape); -1: steps go singly
-    float tiles_us;        // tiles: what a step is estimated to take, and
-    float single_us;       // what a single one is (infinite where it is no choice)
+    float pairs_us;        // what a step is estimated to take so, and what a
+    float single_us;       // single one is (infinite where it is no choice)
 };
 // single steps are chosen within the estimates' error of 4 %
-inline bool singly_ahead(float single_us, float tiles_us) { return single_us < 1.04f * tiles_us; }
+inline bool singly_ahead(float single_us, float pairs_us) { return single_us < 1.04f * pairs_us; }
 
 } // namespace axi
 

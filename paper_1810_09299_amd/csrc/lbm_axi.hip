@@ -1070,7 +1070,16 @@ int pair_strips(int nz, int z_periodic, int waves)
 // 284.  A batch deals whole runs to the XCDs (build_pairs): ten FP64 cases of
 // 256 x 512 fill every XCD but two once in 10 runs each, those two and so the
 // launch twice (105 us a step, singly 83), and all once in 9.
-static void plan_march(const lbm_axi_case *const *cases, int n, bool alone, TwoStepPlan &best)
+struct MarchCost {
+    float launch, row, full;     // us a step: per row of the longest chain, and more by how full the device is
+};
+constexpr MarchCost MARCH_COST[2][4] = {                                // [precision][COLLIDE_*], 5 to 9 % rms
+    {{-4.8f, 1.45f, 0.55f}, {-2.9f, 1.16f, 0.75f}, {-6.7f, 1.54f, 0.39f}, {-4.8f, 1.45f, 0.55f}},   // FP32
+    {{-5.8f, 1.72f, 0.32f}, {-4.5f, 1.48f, 0.27f}, {-5.0f, 1.64f, 0.21f}, {-5.8f, 1.72f, 0.32f}},   // FP64
+};
+
+// sets waves and rows; what a step is estimated to take, in us
+static float plan_march(const lbm_axi_case *const *cases, int n, bool alone, TwoStepPlan &best)
 {
     const bool fp64 = cases[0]->prm.precision == LBM_AXI_FP64, unit = cases[0]->P64.mode == COLLIDE_MRT_UNIT;
     // resident wavefronts per compute unit, by LDS (FP64: more than one per
@@ -1107,18 +1116,21 @@ static void plan_march(const lbm_axi_case *const *cases, int n, bool alone, TwoS
         }
         return *std::max_element(groups, groups + 8);
     };
-    int64_t best_cost = 0;
+    int64_t best_cost = 0, held = 0;
     // every length that a number of equal runs of the tallest case has, from one run on
     for (int rows = max_nr;;) {
-        const int64_t cost = (fullest_xcd(rows) + slots - 1) / slots * (rows + 10);
+        const int64_t groups = fullest_xcd(rows), cost = (groups + slots - 1) / slots * (rows + 10);
         if (!best_cost || cost < best_cost) {
             best_cost = cost;
             best.rows = rows;
+            held = std::min(groups, slots);
         }
         if (rows <= 4) break;
         const int runs = (max_nr + rows - 2) / (rows - 1);
         rows = std::max(4, (max_nr + runs - 1) / runs);
     }
+    const MarchCost c = MARCH_COST[fp64][cases[0]->P64.mode];
+    return c.launch + (float)best_cost * (c.row + c.full * (float)held / (float)slots);
 }
 
 // Marching takes too long to start for what fits the caches: one FP32 case of
@@ -1129,24 +1141,48 @@ static void plan_march(const lbm_axi_case *const *cases, int n, bool alone, TwoS
 // together or in turn; either way a step takes what a launch and the first
 // latencies do and a share per tile of the fullest unit (of the XCD that has
 // most: three cases of 42 x 896 FP32 are 252 tiles of 32 x 16, but 33 on the first
-// XCD's 32 units, 9.2 us a step against 7.1 in 16 x 16; TileCost; fitted, 5 % rms,
-// to 550 cases and batches of 20 to 1200 thousand nodes: 128 x 512 FP32 4.4 in
-// 16 x 16, 5.1 in 12 x 8, 5.8 in 32 x 16; 300 x 600 FP32 9.4 in 12 x 8, 8.0 in
-// 16 x 16, 8.4 in 32 x 16; 256 x 1024 10.0 and 8.9 in the last two, FP64 15.0 and
-// 16.3).
+// XCD's 32 units, 9.2 us a step against 7.1 in 16 x 16), more where many of a
+// case's tiles lie at its rim and take the boundary rules (TileCost; fitted, 4 to
+// 7 % rms, to some 680 cases and batches of 20 to 1250 thousand nodes: 128 x 512
+// FP32 4.4 in 16 x 16, 5.1 in 12 x 8, 5.8 in 32 x 16; 300 x 600 FP32 9.4 in 12 x 8,
+// 8.0 in 16 x 16, 8.4 in 32 x 16; 256 x 1024 10.0 and 8.9 in the last two, FP64
+// 15.0 and 16.3; eight cases of 63 x 608 general MRT FP64 26.6 in 12 x 8, a fifth
+// more per tile than four of 256 x 512).
 // The general and the non-orthogonal MRT hold more registers: in FP64 a unit
 // takes one 16 x 16 tile of theirs at a time, two of the other forms' (256 x 1024
 // non-orthogonal 20.9 us a step in 16 x 16, 17.3 in 32 x 16, 17.5 singly; six cases of
 // 256 x 512 64.4, 52.3, 51.8; SRT 42.8, 49.8, 51.0).
 struct TileCost {
-    float launch, tile;      // us a step
+    float launch, tile, rim;      // us a step; rim: per tile, where all are at the rim
 };
 constexpr TileCost TILE_COST[2][2][TILE_SHAPES] = {                     // [precision][MRT with free rates, non-orthogonal]
-    {{{2.6f, 0.75f}, {2.75f, 0.82f}, {2.65f, 1.8f}, {2.85f, 3.05f}},    // FP32
-     {{2.8f, 0.85f}, {2.8f, 0.95f}, {2.7f, 2.1f}, {2.7f, 3.45f}}},
-    {{{2.5f, 1.2f}, {2.6f, 1.45f}, {2.55f, 3.1f}, {0.65f, 7.5f}},       // FP64
-     {{2.4f, 1.4f}, {2.75f, 1.55f}, {0.95f, 4.85f}, {0.5f, 8.0f}}},
+    {{{2.95f, 0.72f, 0.21f}, {2.95f, 0.78f, 0.33f}, {2.75f, 1.77f, 0.46f}, {2.75f, 3.16f, 0.6f}},   // FP32
+     {{3.0f, 0.83f, 0.24f}, {2.95f, 0.91f, 0.39f}, {2.8f, 2.03f, 0.48f}, {2.75f, 3.5f, 0.75f}}},
+    {{{3.15f, 1.15f, 0.38f}, {2.85f, 1.41f, 0.51f}, {2.4f, 3.23f, 0.45f}, {0.0f, 8.1f, 0.65f}},     // FP64
+     {{2.75f, 1.38f, 0.48f}, {2.85f, 1.51f, 0.62f}, {0.9f, 4.87f, 0.65f}, {0.15f, 8.3f, 0.63f}}},
 };
+
+// us a step in tiles of a shape
+static float tiles_us(const lbm_axi_case *const *cases, int n, int shape, const TileCost &c)
+{
+    const int64_t cus = std::max(1, cases[0]->cus / 8);           // of one XCD
+    int64_t fullest = 0, tiles = 0, plain = 0;                    // each case's are dealt out from the first XCD on
+    with_tile_shape(shape, [&](auto t) {
+        using S = decltype(t);
+        // tiles along an axis of m nodes whose halo stays clear of both ends
+        auto clear = [](int m, int size) { return m < 6 ? 0 : std::max(0, (m - 6) / size - (size + 5) / size); };
+        for (int i = 0; i < n; ++i) {
+            const lbm_axi_params &p = cases[i]->prm;
+            const int64_t tz = (p.nz + S::OZ - 1) / S::OZ, all = tz * ((p.nr + S::OR - 1) / S::OR);
+            fullest += (all + 7) / 8;
+            tiles += all;
+            plain += clear(p.nr, S::OR) * (p.z_periodic ? tz : clear(p.nz, S::OZ));
+        }
+    });
+    const float rim = (float)(tiles - plain) / (float)tiles;
+    return c.launch + (c.tile + c.rim * rim) * (float)((fullest + cus - 1) / cus);
+}
+
 // Single steps take more (5.2 us a step of 64 x 128 FP32, 7.8 of 60 x 286 FP64,
 // 11.1 of 128 x 2048 FP32), but while each of their 64 x 8 tiles has a unit to
 // itself, and the smaller tiles of two steps, by their ragged edges, need a
@@ -1155,30 +1191,45 @@ constexpr TileCost TILE_COST[2][2][TILE_SHAPES] = {                     // [prec
 // Then a step takes a launch and a share per tile by how its rows lie in memory:
 // whole 64-byte lines, half ones, neither (fitted likewise, within 5 %; 256 tiles
 // FP32 6.2 us in rows of 512 nodes, 7.3 of 504, 8.0 of 511).  Batches of more
-// than eight cases were never ahead singly (14 of 30 x 208 FP32 8.7 against 7.3).
+// than eight cases were never ahead singly in one round (14 of 30 x 208 FP32 8.7
+// against 7.3).  Of several rounds single steps were ahead only in batches of
+// small cases, most of whose tiles lie at a rim (161 of 26 x 96 FP32 24.3 against
+// 26.6, eight of 63 x 608 general MRT FP64 24.9 against 26.6).
 struct SingleCost {
-    float launch, line, half, ragged;
+    float launch, line, half, ragged;                             // one round
+    float rounds, round, node, rows;                              // several: also per 100,000 nodes and per 256 ragged tiles
 };
 constexpr SingleCost SINGLE_COST[2][2] = {
-    {{4.6f, 0.0068f, 0.0103f, 0.0125f}, {4.9f, 0.0065f, 0.0101f, 0.0119f}},
-    {{5.9f, 0.0148f, 0.0215f, 0.0244f}, {6.3f, 0.0135f, 0.0209f, 0.024f}},
+    {{4.6f, 0.0068f, 0.0103f, 0.0125f, 4.6f, 1.16f, 2.25f, 1.37f},
+     {4.9f, 0.0065f, 0.0101f, 0.0119f, 4.45f, 1.6f, 2.0f, 1.25f}},
+    {{5.9f, 0.0148f, 0.0215f, 0.0244f, 6.3f, 3.05f, 3.56f, 1.7f},
+     {6.3f, 0.0135f, 0.0209f, 0.024f, 6.6f, 4.1f, 2.75f, 1.76f}},
 };
-constexpr int SINGLY_CASES = 8;
+constexpr int SINGLY_CASES = 8, ROUNDS_CASES = 4;
+// cases of different tables in one launch: pairs pay half of it per step
+constexpr float SEVERAL_CASES = 0.4f;
 
 // us a step of single steps (64 x 8 tiles in 16 bands a case, the default), or
-// infinity where two steps are ahead anyway
-static float single_us(const lbm_axi_case *const *cases, int n, const SingleCost &c)
+// infinity where two steps are ahead anyway; one: whether it is one round
+static float single_us(const lbm_axi_case *const *cases, int n, const SingleCost &c, bool &one)
 {
     const int es = cases[0]->prm.precision == LBM_AXI_FP64 ? 8 : 4, cus = std::max(1, cases[0]->cus / 8);
-    int fullest = 0;                                              // tiles on the first XCD
-    float us = c.launch;
+    int fullest = 0, ragged = 0;                                  // tiles on the first XCD, in rows off whole lines
+    int64_t nodes = 0;
+    float us = c.launch + (n > 1 ? SEVERAL_CASES : 0.0f);
     for (int i = 0; i < n; ++i) {
         const lbm_axi_params &p = cases[i]->prm;
         const int tiles = geom_for(cases[i], 8).tiles, row = p.nz % 64 * es;
         fullest += n == 1 ? (tiles + 7) / 8 : tiles / 16 * 2 + (tiles % 16 > 0) + (tiles % 16 > 8);
         us += (float)tiles * (row % 64 == 0 ? c.line : (row % 32 == 0 ? c.half : c.ragged));
+        nodes += (int64_t)p.nr * p.nz;
+        ragged += row % 64 ? tiles : 0;
     }
-    return n > SINGLY_CASES || fullest > cus ? INFINITY : us;
+    one = fullest <= cus;
+    if (one) return n > SINGLY_CASES ? INFINITY : us;
+    return n < ROUNDS_CASES ? INFINITY
+                            : c.rounds + c.round * (float)fullest / (float)cus + c.node * 1e-5f * (float)nodes +
+                                  c.rows * (float)ragged / 256.0f;
 }
 
 TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool alone)
@@ -1192,27 +1243,25 @@ TwoStepPlan two_step_plan(const lbm_axi_case *const *cases, int n, bool alone)
         plan_march(cases, n, alone, plan);
         return plan;
     }
-    const int64_t cus = std::max(1, cases[0]->cus / 8);           // of one XCD
     const int mode = cases[0]->P64.mode;
     const bool heavy = mode == COLLIDE_MRT || mode == COLLIDE_NMRT;
     for (int shape = 0; shape < TILE_SHAPES; ++shape) {
-        int64_t tiles = 0;                                        // of the fullest XCD: each case's are dealt out evenly
-        with_tile_shape(shape, [&](auto t) {
-            using S = decltype(t);
-            for (int i = 0; i < n; ++i) {
-                const lbm_axi_params &p = cases[i]->prm;
-                tiles += ((int64_t)((p.nz + S::OZ - 1) / S::OZ) * ((p.nr + S::OR - 1) / S::OR) + 7) / 8;
-            }
-        });
-        const TileCost c = TILE_COST[fp64][heavy][shape];
-        const float us = c.launch + c.tile * (float)((tiles + cus - 1) / cus);
-        if (shape == 0 || us <= plan.tiles_us) {
-            plan.tiles_us = us;
+        const float us = tiles_us(cases, n, shape, TILE_COST[fp64][heavy][shape]);
+        if (shape == 0 || us <= plan.pairs_us) {
+            plan.pairs_us = us;
             plan.tile = shape;
         }
     }
-    plan.single_us = single_us(cases, n, SINGLE_COST[fp64][heavy]);
-    if (alone && singly_ahead(plan.single_us, plan.tiles_us)) plan.tile = -1;
+    bool one;
+    plan.single_us = single_us(cases, n, SINGLE_COST[fp64][heavy], one);
+    if (!one && plan.single_us < 1.15f * plan.pairs_us) {
+        // tiles hardly pay: then the march may (161 cases of 26 x 96 FP32 21.9 us a step)
+        TwoStepPlan march = plan;
+        march.march = true;
+        march.pairs_us = plan_march(cases, n, alone, march);
+        if (march.pairs_us < plan.pairs_us && !singly_ahead(plan.single_us, march.pairs_us)) return march;
+    }
+    if (alone && singly_ahead(plan.single_us, plan.pairs_us)) plan.tile = -1;
     return plan;
 }
 

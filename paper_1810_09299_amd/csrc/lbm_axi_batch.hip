@@ -476,7 +476,7 @@ void build_pairs(lbm_axi_batch *b, const std::vector<int> &order)
     b->pair_work.clear();
     for (int q = 0; q <= NMODE; ++q) b->pair_start[q] = 0;
     if (b->precision == LBM_AXI_FP16D) return;
-    float tiles_us = 0.0f, single_us = 0.0f;         // of a step, all forms
+    float pairs_us = 0.0f, single_us = 0.0f;         // of a step, all forms
     for (size_t first = 0, end; first < order.size(); first = end) {
         const int mode = b->cases[order[first]]->P64.mode;
         std::vector<const lbm_axi_case *> form;
@@ -484,7 +484,7 @@ void build_pairs(lbm_axi_batch *b, const std::vector<int> &order)
             form.push_back(b->cases[order[end]]);
         const TwoStepPlan plan = two_step_plan(form.data(), (int)form.size(), false);
         b->plan[mode] = plan;
-        tiles_us += plan.tiles_us;
+        pairs_us += plan.pairs_us;
         single_us += plan.single_us;
         std::vector<WorkItem> queue[8];
         int next = 0;
@@ -512,7 +512,7 @@ void build_pairs(lbm_axi_batch *b, const std::vector<int> &order)
     }
     // few cases may be ahead singly (every launch flips the phase of all: all
     // forms go one way)
-    if (singly_ahead(single_us, tiles_us)) b->pair_work.clear();
+    if (singly_ahead(single_us, pairs_us)) b->pair_work.clear();
     // both lists share the reserved area
     if (b->work.size() + b->pair_work.size() > (size_t)MAX_WORK) b->pair_work.clear();
 }

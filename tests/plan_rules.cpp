@@ -22,7 +22,7 @@ int main()
         }
         const axi::TwoStepPlan p = axi::two_step_plan(ptrs.data(), n, alone != 0);
         // tile -1: singly (a batch of one collision form decides as build_pairs does)
-        const bool singly = !p.march && (p.tile < 0 || (!alone && axi::singly_ahead(p.single_us, p.tiles_us)));
+        const bool singly = !p.march && (p.tile < 0 || (!alone && axi::singly_ahead(p.single_us, p.pairs_us)));
         printf("%d %d %d %d %d\n", (int)p.march, p.waves, p.rows, singly ? -1 : p.tile, axi::default_tile(ptrs[0]));
     }
     return 0;

@@ -79,14 +79,14 @@ def test_march_of_a_batch_goes_by_its_fullest_xcd(plan_of, precision, resident, 
     assert cost(p["rows"]) == min(best, cost(4))
 
 
-# us a step as measured on an MI355X: single steps, tiles of 8 x 4, 12 x 8, 16 x 16, 32 x 16
+# us a step as measured on an MI355X: single steps, tiles of 8 x 4, 12 x 8, 16 x 16, 32 x 16 (marching)
 MEASURED = [
     ("fp64", NMRT, [(256, 1024, True)], True, (17.3, 46.5, 19.04, 20.67, 17.32)),
     ("fp64", MRT, [(512, 1024, True)], True, (35.86, 91.37, 35.55, 39.18, 33.45)),
     ("fp64", NMRT, [(400, 700, True)], True, (25.76, 49.87, 20.25, 23.96, 22.63)),
     ("fp64", NMRT, [(256, 512, True)] * 4, False, (36.23, 93.63, 37.46, 41.04, 33.96)),
-    ("fp64", MRT, [(256, 512, True)] * 6, False, (52.11, 142.39, 56.01, 64.57, 52.88)),
-    ("fp64", MRT, [(100, 200, True)] * 30, False, (51.42, 117.78, 49.21, 61.1, 57.71)),
+    ("fp64", MRT, [(256, 512, True)] * 6, False, (52.11, 142.39, 56.01, 64.57, 52.88, 48.76)),
+    ("fp64", MRT, [(100, 200, True)] * 30, False, (51.42, 117.78, 49.21, 61.1, 57.71, 42.03)),
     ("fp64", SRT, [(256, 512, True)] * 6, False, (51.03, 119.46, 51.8, 42.78, 49.79)),
     ("fp64", UNIT, [(512, 1024, True)], True, (36.14, 76.27, 32.4, 26.29, 31.46)),
     ("fp32", NMRT, [(512, 1024, True)], True, (20.18, 55.78, 23.1, 19.04, 16.61)),
@@ -108,6 +108,12 @@ MEASURED = [
     ("fp32", NMRT, [(125, 784, True)], False, (6.36, 14.4, 7.85, 7.31, 6.7)),
     ("fp32", UNIT, [(382, 224, True)], False, (5.81, 11.01, 6.1, 6.05, 6.05)),
     ("fp32", UNIT, [(30, 208, True)] * 14, False, (8.66, 13.48, 7.3, 7.93, 7.37)),
+    # small cases, most of their tiles at a rim
+    ("fp32", UNIT, [(26, 96, True)] * 161, False, (24.29, 51.93, 26.62, 26.72, 26.89, 21.93)),
+    ("fp32", NMRT, [(24, 400, False)] * 59, False, (28.24, 68.96, 28.95, 32.37, 34.19, 26.14)),
+    ("fp64", MRT, [(63, 608, True)] * 8, False, (24.92, 63.95, 26.55, 27.74, 27.16, 29.05)),
+    ("fp64", MRT, [(46, 176, True)] * 80, False, (59.17, 137.74, 58.65, 68.28, 73.81, 44.19)),
+    ("fp64", NMRT, [(278, 128, True)] * 12, False, (33.11, 79.96, 33.32, 35.55, 33.65, 29.22)),
 ]
 
 
@@ -116,9 +122,9 @@ def test_tiles_follow_the_measured_times(plan_of, precision, mode, grids, alone,
     """The plan loses no more than the cost model's error (5 %) to single steps,
     and no more than twice that to the best tile shape."""
     p = plan_of(precision, grids, alone=alone, mode=mode)
-    assert not p["march"]
-    assert us[p["tile"] + 1] <= 1.05 * us[0]
-    assert us[p["tile"] + 1] <= 1.1 * min(us)
+    got = us[5] if p["march"] else us[p["tile"] + 1]
+    assert got <= 1.05 * us[0]
+    assert got <= 1.1 * min(us[:5])
 
 
 # FP16-deviation storage, us a step as measured in 64 x 4 and 64 x 8 tiles
