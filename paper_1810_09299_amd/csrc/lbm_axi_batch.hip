@@ -8,7 +8,7 @@
 //
 // FP64 and FP32 batches advance two steps per launch where both are wanted
 // (build_pairs: marching strips or tiles, by size); the odd step out, every step
-// in FP16-deviation storage, of few cases that are ahead singly, or recorded by
+// in FP16-deviation storage, of cases that are ahead singly, or recorded by
 // the caller, is a launch of batch_step_kernel(_h) over the work list (one per
 // collision form present, see COLLIDE_*): item w = (slot, tile) runs the same
 // tile body as the single-case kernel.  Either way every
@@ -463,10 +463,10 @@ bool ramping_at(const lbm_axi_case *c, int64_t t)
 }
 
 // The work lists of the two-step launches for the running cases (`order`:
-// grouped by collision form), or none: of few cases that are ahead singly, and
-// in FP16-deviation storage (a second step in the launch pays its encoding and
-// decoding again, on the halo too; in tiles 150 x 300 took 6.4 us a step against
-// 5.6 singly, 256 x 512 8.9 against 5.9).  Marching, the strips of one run of
+// grouped by collision form), or none: of cases that are ahead singly, and in
+// FP16-deviation storage (tried in tiles, whose halo pays encoding and decoding
+// again: 150 x 300 6.4 us a step against 5.6 singly, 256 x 512 8.9 against 5.9;
+// the march was not built for it).  Marching, the strips of one run of
 // rows go to one XCD (they share the lines at their edges; dealt singly, 20
 // cases of 200 x 500 FP64 took 101.2 us a step against 100.1, 64 of 256 x 448
 // FP32 159.6 against 158.7), run after run round the XCDs; tiles go as eight runs
@@ -510,8 +510,8 @@ void build_pairs(lbm_axi_batch *b, const std::vector<int> &order)
             for (const auto &x : queue) b->pair_work.push_back(l < x.size() ? x[l] : WorkItem{-1, 0, 0, 0});
         for (int q = mode + 1; q <= NMODE; ++q) b->pair_start[q] = (int)b->pair_work.size();
     }
-    // few cases may be ahead singly (every launch flips the phase of all: all
-    // forms go one way)
+    // singly where that is ahead (every launch flips the phase of all: all forms
+    // go one way)
     if (singly_ahead(single_us, pairs_us)) b->pair_work.clear();
     // both lists share the reserved area
     if (b->work.size() + b->pair_work.size() > (size_t)MAX_WORK) b->pair_work.clear();
