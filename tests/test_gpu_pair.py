@@ -144,16 +144,20 @@ def test_live_steps_between_replays(precision, nr, nz):
     with torch.cuda.graph(steps, stream=stream):
         c.step(2)
     done = 6
+
+    def replay(graph):                                # on the case's stream, after its live steps
+        with torch.cuda.stream(stream):
+            graph.replay()
+
     for live in ((2,), (6,), (50,), (3, 5), (0,), (7, 1, 2)):
-        steps.replay()
-        torch.cuda.synchronize()
+        replay(steps)
         for n in live:
             c.step(n)
         done += 2 + sum(live)
         while ref.t < done:
             ref.step(1)
         want = ref.moments()[0]
-        read.replay()
+        replay(read)
         torch.cuda.synchronize()
         got = c.moments()[0]
         for o, k in zip(out, FIELDS):
